@@ -152,6 +152,13 @@ __device__ __forceinline__ int sum32i(int v) {
   return (int)(r[0] + r[1]);
 }
 
+// Waits until this wave's own stores and atomics have been performed.  A
+// workgroup barrier does not wait for them (a workgroup's waves share one
+// CU, so workgroup scope needs no global-memory wait): before a wave
+// arrives at a counter that other workgroups read, every wave that stored
+// data for them takes this wait, then the workgroup barrier.
+__device__ __forceinline__ void wait_own_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // bit pattern of a non-negative float (including +inf) keeps its order as uint
 __device__ __forceinline__ void atomic_max_nonneg(float* addr, float v) {
   atomicMax(reinterpret_cast<unsigned int*>(addr), __float_as_uint(v));

@@ -49,6 +49,7 @@ constexpr int kVisSlice = 8192;                         // tokens per visible-co
 // one arrival and waits until the arrivals reach `target`.  Returns false
 // (in every thread) if the wait timed out or another block gave up.
 __device__ bool grid_barrier(int* ctrl, int target, long long timeout, int* s_ok) {
+  wait_own_stores();
   __syncthreads();
   if (threadIdx.x == 0) {
     __threadfence();
@@ -78,9 +79,10 @@ __device__ bool grid_barrier(int* ctrl, int target, long long timeout, int* s_ok
 // The same barrier without the fences: for phases whose cross-workgroup
 // data moves only through agent-scope atomics (a fence writes back and
 // invalidates the whole L2 of the workgroup's XCD, which costs more than
-// a round's work).  __syncthreads() first waits for the workgroup's own
-// memory operations, so its atomics are performed before the arrival.
+// a round's work).  Every wave waits for its own stores before the workgroup
+// barrier, so they are performed before the arrival.
 __device__ bool grid_barrier_nofence(int* ctrl, int target, long long timeout, int* s_ok) {
+  wait_own_stores();
   __syncthreads();
   if (threadIdx.x == 0) {
     __hip_atomic_fetch_add(&ctrl[kBarrier], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

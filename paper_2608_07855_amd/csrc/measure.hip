@@ -913,9 +913,9 @@ __global__ __launch_bounds__(kNW * 64, 1) void page_kernel(AttnGeom a, PageWork 
 // finishes last (an arrival count per pair) adds the parts in order (so the
 // result does not depend on scheduling) and takes the ratio.  The sums cross
 // workgroups through agent-scope atomic stores and loads, which bypass the
-// per-XCD L2, so no cache-wide fence is needed; the workgroup barrier before
-// the arrival waits for the stores.  Weights are taken relative to the row's
-// log-sum-exp (every weight <= 1).
+// per-XCD L2, so no cache-wide fence is needed; every wave waits for
+// its own stores before the workgroup barrier that precedes the arrival.
+// Weights are taken relative to the row's log-sum-exp (every weight <= 1).
 // ---------------------------------------------------------------------------
 constexpr int kFixT = 256;        // threads of a fix-up workgroup
 constexpr int kFixGrid = 1024;    // (pair, part) items in flight
@@ -1209,6 +1209,7 @@ __device__ __forceinline__ void page_fixup_body(const AttnGeom& a, const AttnSpl
       __hip_atomic_store(reinterpret_cast<unsigned*>(out + i), __float_as_uint(v), __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
     }
+    wait_own_stores();   // the sums are performed before the arrival
     __syncthreads();
     if (tid == 0)
       sLast = __hip_atomic_fetch_add(&arrive[e], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1;

@@ -185,6 +185,7 @@ __device__ void choose_digit(const SelectArgs& a, int s, int p, int* tmp) {
 // arrival at the end of a histogram launch; true in the last workgroup of
 // sequence s (all threads)
 __device__ bool arrive_last(int32_t* counter, int n_blocks, int* s_flag) {
+  wait_own_stores();
   __syncthreads();
   if (threadIdx.x == 0) {
     __threadfence();
@@ -478,8 +479,8 @@ __device__ __forceinline__ void hist_add1(unsigned int* hist, uint32_t bin, bool
 // word that crosses workgroups (control words, histograms, the candidate
 // list, chunk counts, n_kept) moves through agent-scope atomics, so the
 // barrier needs no fence (one writes back and invalidates the whole L2 of
-// the workgroup's XCD); the workgroup barrier before an arrival waits for
-// the workgroup's own memory operations.
+// the workgroup's XCD); every wave waits for its own stores before the
+// workgroup barrier that precedes an arrival.
 // ---------------------------------------------------------------------------
 namespace {
 constexpr int kQT = 256;
@@ -493,6 +494,7 @@ enum { qArrive = 0, qDone = 1, qNP = 2, qNF = 3, qNotLo = 4, qHi = 5, qError = 6
 constexpr int kCandMax = kSelBins;
 
 __device__ bool seq_barrier(int* ctrl, int target, long long timeout, int* s_ok) {
+  wait_own_stores();
   __syncthreads();
   if (threadIdx.x == 0) {
     __hip_atomic_fetch_add(&ctrl[qArrive], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -939,6 +941,7 @@ __global__ __launch_bounds__(kQT) void select_grid(SelectArgs a) {
   }
   // the last workgroup of the sequence clears the control words and the
   // histograms for the next call (every other workgroup is done with them)
+  wait_own_stores();
   __syncthreads();
   if (tid == 0) s_ok = __hip_atomic_fetch_add(&ctrl[qDone], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == C - 1;
   __syncthreads();
