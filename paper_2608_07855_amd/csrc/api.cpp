@@ -30,8 +30,6 @@ constexpr int kMaxDevices = 64;
 constexpr int kPinnedSlots = 4;
 constexpr int kPageCacheEntries = 16;
 constexpr float kLog2eHost = 1.4426950408889634f;   // log2(e): natural-log LSE to log2 units
-constexpr int kJointWindow = 32;       // candidates tested per joint round
-constexpr int kJointRowsPerBlock = 64;
 constexpr int kTargetBlocks = 256;     // one 8-wave workgroup per compute unit
 // the fix-up recomputes a dominant page's whole split for one row, so long
 // splits make it expensive: splits hold at most this many tokens
@@ -1023,14 +1021,13 @@ extern "C" int ckv_joint_test(ckv_ctx* c, const ckv_kv_view* kv, const ckv_windo
   j.max_cand = max_cand;
   j.W = a.W;
   j.n_cand = n_cand;
-  j.window = kJointWindow;
-  j.rows_per_block = kJointRowsPerBlock;
   j.tau = tau_joint;
   j.nonfinite = c->nf_dev;
   j.barrier_ticks = c->barrier_ticks;
   j.accept_all = (c->policy & CKV_POLICY_NO_JOINT) != 0;
   j.accepted = accepted;
-  j.union_R = union_R;
+  j.ur = union_R;
+  j.want_union = union_R != nullptr;
   j.n_accepted = n_accepted;
   j.o = o;
   j.pos = a.pos;
@@ -1042,22 +1039,27 @@ extern "C" int ckv_joint_test(ckv_ctx* c, const ckv_kv_view* kv, const ckv_windo
   j.lse = lse;
   j.n_pages = pages->n_pages;
   j.cand = cand;
-  float *resid, *resA, *Dst, *Ast;
-  int *resC, *Cst;
+  float *resid, *resA;
+  int* resC;
   Plan plan;
-  plan.add(&j.onorm, total_rows);
   plan.add(&j.nvis_part, (size_t)a.W * j.n_vis_slices);
   plan.add(&resid, (size_t)max_cand * total_rows * D);
   plan.add(&resA, (size_t)max_cand * total_rows);
   plan.add(&resC, (size_t)max_cand * total_rows);
-  plan.add(&Dst, 2 * (size_t)total_rows * D);
-  plan.add(&Ast, 2 * (size_t)total_rows);
-  plan.add(&Cst, 2 * (size_t)total_rows);
+  if (joint_state_global(total_rows)) {
+    plan.add(&j.st_D, (size_t)total_rows * D);
+    plan.add(&j.st_A, total_rows);
+    plan.add(&j.st_C, total_rows);
+    plan.add(&j.st_on, total_rows);
+    plan.add(&j.st_nv, total_rows);
+    plan.add(&j.st_fix, 2 * (size_t)total_rows);
+  }
   plan.add(&j.ctrl, 8);
-  plan.add(&j.rbuf, kJointWindow);
-  plan.add(&j.bmax, (size_t)kTargetBlocks * kJointWindow);
-  plan.add(&j.in_acc, std::max(pages->n_pages, 1));
-  plan.add(&j.fix_list, 2 * (size_t)kJointWindow * total_rows);
+  plan.add(&j.bmax, ckv::kJointBmaxWords);
+  if (!union_R) plan.add(&j.ur, max_cand);
+  plan.add(&j.acc_t, std::max(pages->n_pages, 1));
+  j.fix_cap = 2 * ckv::kJointWindow * total_rows;
+  plan.add(&j.fix_list, 2 * (size_t)j.fix_cap);
   plan.add(&j.fpart, (size_t)ckv::kJointFixItems * (D + 1));
   const int32_t *dstart = nullptr, *dlen = nullptr;
   if ((rc = page_table(c, pages, &dstart, &dlen))) return rc;
@@ -1067,9 +1069,6 @@ extern "C" int ckv_joint_test(ckv_ctx* c, const ckv_kv_view* kv, const ckv_windo
   j.resid = resid;
   j.resA = resA;
   j.resC = resC;
-  j.Dstate = Dst;
-  j.Astate = Ast;
-  j.Cstate = Cst;
 
   // Nothing here reads the candidate count on the host: the kernels read
   // *n_cand and size their work from it (max_cand bounds the launches).
@@ -1095,7 +1094,7 @@ extern "C" int ckv_joint_test(ckv_ctx* c, const ckv_kv_view* kv, const ckv_windo
     CKV_LAUNCH(c, "joint_residual", launch_page_kernel(a, pw, rs, 1, max_page_len(pages), c->stream));
   }
   // with no pages the joint kernel only writes the outputs
-  CKV_LAUNCH(c, "joint_round", launch_joint_persistent(j, kTargetBlocks, c->stream));
+  CKV_LAUNCH(c, "joint_round", launch_joint(j, c->stream));
   return CKV_OK;
 }
 

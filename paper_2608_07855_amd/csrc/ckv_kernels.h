@@ -207,29 +207,31 @@ struct JointArgs {
   const float* resid;     // [rows][max_cand][D]
   const float* resA;      // [rows][max_cand]
   const int* resC;
-  float* onorm;           // [rows]: ||o_p|| (phase 0)
-  int* nvis_part;         // [W][n_vis_slices]: visible tokens of window row p per slice (phase 0)
+  int* nvis_part;         // [W][n_vis_slices]: visible tokens of window row p per slice
   int n_vis_slices;
   const float* o;         // [rows][D] window outputs
   const int32_t* pos;     // [S] token positions
   const int32_t* qpos;    // [W] window positions
   int S;
   int test_cap;           // candidates tested at most (0: none, e.g. no pages)
-  float* Dstate;          // [rows][D] accumulated residual of accepted pages
-  float* Astate;          // [rows]
-  int* Cstate;            // [rows]
-  int* ctrl;              // [8]: cursor, pending accepted item, barrier arrivals, error, parity
-                          //      (zero before the launch: the residual pass clears them)
-  unsigned int* rbuf;     // [window] per-candidate max ratio bits
-  unsigned int* bmax;     // [workgroups][window] per-workgroup candidate maxima (owned-row form)
-  int window;             // candidates evaluated per round
-  int rows_per_block;
+  // the rows' state when it does not fit LDS (joint_state_global), else null:
+  // accumulated residual [rows][D], mass, visible count, ||o_p||, visible
+  // tokens [rows] and fix-up bits [rows][2]
+  float* st_D;
+  float* st_A;
+  int* st_C;
+  float* st_on;
+  int* st_nv;
+  unsigned long long* st_fix;
+  int* ctrl;              // [8] control words (zero before the launch: the residual pass clears them)
+  unsigned int* bmax;     // [256 workgroups][2 guesses][window] maxima of a round
   float tau;
-  long long barrier_ticks; // bound of a grid-barrier wait (100 MHz wall clock ticks)
+  long long barrier_ticks; // bound of a grid-wide wait (100 MHz wall clock ticks)
   uint32_t* nonfinite;    // latched when an o or lse row is NaN or infinite (or null)
   int accept_all;         // no Eq. (11) gate: every candidate accepted
+  int want_union;         // the caller reads the union effects
   uint8_t* accepted;
-  float* union_R;
+  float* ur;              // [max_cand] union effects: the caller's array or workspace
   int32_t* n_accepted;
   // recomputation by definition of (candidate, row) pairs whose union mass
   // exceeds kJointFixA (Eq. (6) is ill-conditioned there)
@@ -239,15 +241,18 @@ struct JointArgs {
   const int32_t* plen;
   int n_pages;
   const int32_t* cand;    // [max_cand] page of each candidate
-  uint8_t* in_acc;        // [n_pages] accepted so far (phase 0 clears it)
-  int* fix_list;          // [window * rows] (slot, row) pairs flagged in a round
+  int32_t* acc_t;         // [n_pages] the candidate that was accepted with this page (INT_MAX: none)
+  int* fix_list;          // [fix_cap] (candidate, row) pairs left to the fix-up
+  int fix_cap;            // 2 * window * rows: a round adds at most window * rows
   float* fpart;           // [kJointFixItems][D + 1] partial sums of the fix-up
 };
+constexpr int kJointWindow = 32;        // candidates tested per round
+constexpr int kJointBmaxWords = 256 * 2 * kJointWindow;
 constexpr float kJointFixA = 0.8f;      // union mass above which a pair is recomputed
-constexpr int kJointFixItems = 32768;   // (pair, part) items of the fix-up workspace
-constexpr int kJointFixParts = 16;      // parts a pair's row is split into at most
+constexpr int kJointFixItems = 30720;   // (pair, segment) items of the fix-up workspace
 int joint_vis_slices(int S);
-hipError_t launch_joint_persistent(const JointArgs& j, int max_blocks, hipStream_t s);
+bool joint_state_global(int total_rows);
+hipError_t launch_joint(const JointArgs& j, hipStream_t s);
 
 // checkpoint: protection, selection, compaction (Eq. (12)-(13), Eq. (4))
 // pages retired on the device: page cand[i] (i < min(*n_cand, max_cand))

@@ -7,32 +7,49 @@
 // candidate by the page kernel in residual mode) and the running sums
 // D = sum_{E in A} r_E, A_A = sum_{E in A} A_E over the accepted set A.
 //
-// The greedy loop is evaluated in speculative rounds: a round tests the next
-// `window` candidates against the same accepted set (each test is exact,
-// because all earlier candidates are decided); the first one that passes is
-// accepted, the ones before it are rejected, and the ones after it are
-// tested again in the next round.  The accepted candidate's residual is
-// folded into the state by the next round while it copies the state into
-// the other buffer (double buffering, so no block reads a row another block
-// is writing).
+// The greedy loop is evaluated in speculative rounds.  A round tests the next
+// kJointWindow candidates under two guesses at once, from one read of their
+// residuals: every candidate alone against the accepted set ("independent",
+// right as long as the ones before it are rejected), and every candidate on
+// top of all earlier ones of the round ("chain", right as long as those are
+// accepted; the sums are added in the order in which single acceptances would
+// add them).  The decision takes the chain up to its first failure, which it
+// rejects, or, when the first candidate fails, the rejections up to the first
+// candidate that passes, which it accepts.  Candidates come in the order of
+// their own effects, so a call is mostly one run of acceptances and then
+// rejections, and nearly every round decides many: the case of 206 candidates
+// and 42-54 acceptances (32768 tokens, 2048 window rows) takes 9-14 rounds
+// where testing against the accepted set alone took one per acceptance.
 //
 // All rounds run in one launch of at most as many workgroups as the device
-// holds at once: phase 0 clears the state and computes ||o_p|| and the
-// visible-token counts, then a grid barrier ends each round's tests, block 0
-// takes the decision, and a second barrier publishes it.  The candidate count
-// is read on the device, so the call needs no host round trip; each round
-// decides at least one candidate, so the loop ends within max_cand rounds.
-// A barrier wait is bounded: if the workgroups cannot all run at once (a
-// device shared with other work), every block leaves and *n_accepted = -1.
+// holds at once.  Workgroup b owns the window rows [b * rpb, (b + 1) * rpb)
+// for the whole call and keeps their state (D, A_A, visible counts) to
+// itself, in LDS (or its own part of global memory when a workgroup owns
+// more than kRowsOwnedMax rows), so a round reads only the candidates'
+// residual rows and publishes one maximum per candidate and guess.  The
+// workgroup that arrives last reduces the maxima, decides and publishes the
+// decision in one 64-bit word that the others poll: one grid-wide wait per
+// round.  Everything that crosses workgroups moves through agent-scope
+// atomics, so no fence (which would write back and invalidate the XCD's
+// whole L2) is needed.  The candidate count is read on the device, so the
+// call needs no host round trip; each round decides at least one candidate,
+// so the loop ends within max_cand rounds.  A wait is bounded: if the
+// workgroups cannot all run at once (a device shared with other work), every
+// block leaves and *n_accepted = -1.
 //
 // A union that holds nearly all of a row's attention mass makes Eq. (6)
 // ill-conditioned: o - o^{\X} = D / (1 - A_X) divides float32 cancellation
 // by a small 1 - A_X.  A (candidate, row) pair whose union mass exceeds
-// kJointFixA is therefore left out of the closed form and listed; after the
-// round's tests every workgroup recomputes the listed pairs by definition --
+// kJointFixA is left out of the closed form and recomputed by definition --
 // the row's output over the tokens outside the union, o', in float32 from
 // the keys and values -- and the ratio ||o - o'|| / ||o|| joins the
-// candidate's maximum before the decision.
+// candidate's maximum.  The union of candidate t is t and the accepted
+// candidates before t, which the final decisions determine, so pairs of
+// decided candidates are listed and recomputed together after the last
+// round (they only enter union_R: a candidate whose other rows already
+// exceed tau is rejected whatever they give).  A candidate that only such
+// pairs can decide is resolved at once.  Pairs of candidates a round tested
+// but did not decide are dropped.
 #include "ckv_device.h"
 #include "ckv_kernels.h"
 
@@ -41,305 +58,404 @@
 
 namespace ckv {
 
-// control words (cleared by the residual pass before this kernel starts)
-enum { kCursor = 0, kPending = 1, kBarrier = 2, kError = 3, kParity = 4, kFixN = 5 };
-constexpr int kVisSlice = 8192;                         // tokens per visible-count item
+// control words (cleared by the residual pass before this kernel starts):
+// arrivals, error, listed pairs, and the 64-bit decision word (round << 32 | payload)
+enum { kArrive = 0, kError = 1, kFixN = 2, kWord = 4 };
+// payload of a decision: mode (1: chain) | n << 1 | extra << 7 | flags
+constexpr unsigned kDecChain = 1u, kDecExtra = 1u << 7, kDecResolve = 1u << 8, kDecDefer = 1u << 9,
+                   kDecFlush = 1u << 10;
+constexpr int kVisSlice = 8192;        // tokens per visible-count item
+constexpr int kJT = 512, kJW = kJT / 64;   // threads and waves of a workgroup
+constexpr int kRowsOwnedMax = 64;      // rows whose state a workgroup keeps in LDS
+constexpr int kJointBlocksMax = 256;   // workgroups at most (one per compute unit)
+constexpr int kCandBatch = 16;         // candidates reduced together
+constexpr int kFixSegMax = 1024;       // tokens of a row per fix-up item at most
+static_assert(kJointWindow == 2 * kCandBatch, "a round's maxima fill one wave: window x 2 guesses");
 
-// Grid barrier: thread 0 of every block publishes the block's writes, adds
-// one arrival and waits until the arrivals reach `target`.  Returns false
-// (in every thread) if the wait timed out or another block gave up.
-__device__ bool grid_barrier(int* ctrl, int target, long long timeout, int* s_ok) {
-  wait_own_stores();
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __threadfence();
-    atomicAdd(&ctrl[kBarrier], 1);
-    const long long t0 = wall_clock64();
-    int ok = 1;
-    if (timeout <= 0) {   // a zero bound gives up at once: the failure path, forced
-      __hip_atomic_store(&ctrl[kError], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      ok = 0;
-    }
-    while (ok && __hip_atomic_load(&ctrl[kBarrier], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-      if (__hip_atomic_load(&ctrl[kError], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
-          wall_clock64() - t0 >= timeout) {
-        __hip_atomic_store(&ctrl[kError], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        ok = 0;
-        break;
-      }
-      __builtin_amdgcn_s_sleep(2);
-    }
-    __threadfence();
-    *s_ok = ok;
-  }
-  __syncthreads();
-  return *s_ok != 0;
+template <class T>
+__device__ __forceinline__ T ld_agent(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T>
+__device__ __forceinline__ void st_agent(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The same barrier without the fences: for phases whose cross-workgroup
-// data moves only through agent-scope atomics (a fence writes back and
-// invalidates the whole L2 of the workgroup's XCD, which costs more than
-// a round's work).  Every wave waits for its own stores before the workgroup
-// barrier, so they are performed before the arrival.
-__device__ bool grid_barrier_nofence(int* ctrl, int target, long long timeout, int* s_ok) {
+// Arrival of this workgroup; true in the workgroup that completes `target`
+// arrivals.  Every wave first waits for its own stores.
+__device__ bool joint_arrive(int* ctrl, int target, int* s_flag) {
   wait_own_stores();
   __syncthreads();
+  if (threadIdx.x == 0)
+    *s_flag = __hip_atomic_fetch_add(&ctrl[kArrive], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == target - 1;
+  __syncthreads();
+  return *s_flag != 0;
+}
+
+// Thread 0 polls `ready` until it holds, the bound runs out or another
+// workgroup gave up; false (in every thread) in the last two cases.
+template <class F>
+__device__ bool joint_wait(int* ctrl, long long timeout, int* s_flag, F ready) {
   if (threadIdx.x == 0) {
-    __hip_atomic_fetch_add(&ctrl[kBarrier], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const long long t0 = wall_clock64();
     int ok = 1;
     if (timeout <= 0) {   // a zero bound gives up at once: the failure path, forced
-      __hip_atomic_store(&ctrl[kError], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      st_agent(&ctrl[kError], 1);
       ok = 0;
     }
-    while (ok && __hip_atomic_load(&ctrl[kBarrier], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-      if (__hip_atomic_load(&ctrl[kError], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
-          wall_clock64() - t0 >= timeout) {
-        __hip_atomic_store(&ctrl[kError], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    while (ok && !ready()) {
+      if (ld_agent(&ctrl[kError]) != 0 || wall_clock64() - t0 >= timeout) {
+        st_agent(&ctrl[kError], 1);
         ok = 0;
         break;
       }
       __builtin_amdgcn_s_sleep(1);
     }
-    *s_ok = ok;
+    *s_flag = ok;
   }
   __syncthreads();
-  return *s_ok != 0;
+  const bool ok = *s_flag != 0;
+  __syncthreads();
+  return ok;
+}
+
+__device__ bool joint_barrier(int* ctrl, int target, long long timeout, int* s_flag) {
+  joint_arrive(ctrl, target, s_flag);
+  __syncthreads();
+  return joint_wait(ctrl, timeout, s_flag, [&] { return ld_agent(&ctrl[kArrive]) >= target; });
 }
 
 __device__ __forceinline__ void store_pair(int* p, int2 v) {
-  __hip_atomic_store(p, v.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __hip_atomic_store(p + 1, v.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  st_agent(p, v.x);
+  st_agent(p + 1, v.y);
 }
-__device__ __forceinline__ int2 load_pair(const int* p) {
-  return make_int2(__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
-                   __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+__device__ __forceinline__ int2 load_pair(const int* p) { return make_int2(ld_agent(p), ld_agent(p + 1)); }
+
+// v[0..31] per lane -> the sum over the wave's 64 lanes of value lane / 2
+// (each exchange step keeps half of the values).  The order of the additions
+// is that of a butterfly over lane offsets 32, 16, 8, 4, 2, 1.
+__device__ __forceinline__ float reduce_scatter32(float (&v)[32], int lane) {
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 16]), false, false);
+    v[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 8]), false, false);
+    v[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+#pragma unroll
+  for (int off = 8, n = 4; off >= 2; off >>= 1, n >>= 1) {
+    const bool up = (lane & off) != 0;
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+      const float mine = up ? v[i + n] : v[i], other = up ? v[i] : v[i + n];
+      v[i] = mine + __shfl_xor(other, off, 64);
+    }
+  }
+  return v[0] + __shfl_xor(v[0], 1, 64);
 }
 
-// One candidate x row-block test item of a round (the body of a round):
-// item (jx, rb) tests candidate cursor + jx on the rows of block rb and
-// raises rbuf[jx] to its largest ratio; items with jx == 0 also copy the
-// state (with the pending accepted residual folded in) into the other buffer.
-__device__ void joint_item(const JointArgs& j, const RowStats& rs, int jx, int rb, int cursor, int pend,
-                           int par, int n_eff, unsigned int* smax) {
-  const int t = cursor + jx;
-  const bool valid = t < n_eff;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r0 = rb * j.rows_per_block;
-  const int r1 = min(j.total_rows, r0 + j.rows_per_block);
-  const size_t RD = (size_t)j.total_rows * j.D;
-  const float* Din = j.Dstate + (size_t)par * RD;
-  float* Dout = j.Dstate + (size_t)(par ^ 1) * RD;
-  const float* Ain = j.Astate + (size_t)par * j.total_rows;
-  float* Aout = j.Astate + (size_t)(par ^ 1) * j.total_rows;
-  const int* Cin = j.Cstate + (size_t)par * j.total_rows;
-  int* Cout = j.Cstate + (size_t)(par ^ 1) * j.total_rows;
-  if (threadIdx.x == 0) *smax = 0u;
-  __syncthreads();
-  float wmax = 0.f;
-  // a wave takes RB rows at a time (rows w, w + 4, ...) and issues every
-  // load of the RB rows before the first use, so the rows' memory
-  // latencies overlap instead of adding up
-  constexpr int RB = 4, KD = 4;   // rows in flight per wave; width chunks of 64 (D <= 256)
-  for (int base = r0 + wave; base < r1; base += 4 * RB) {
-    float dv[RB][KD], rv[RB][KD], tv[RB][KD];
-    float Acur[RB], At[RB], on[RB];
-    int Ccur[RB], Ct[RB], nv[RB];
+// The state of the workgroup's rows: in LDS, or in its rows' part of global
+// memory.  A row belongs to one wave, and every lane writes what it reads
+// back (A, C, onorm, nvis, the fix bits: all lanes the same value).
+struct RowState {
+  float* D;                   // [nr][D]
+  float* A;
+  int* C;
+  float* onorm;
+  int* nvis;
+  unsigned long long* fix;    // [nr][2]: pairs left to the fix-up, bit 2 * candidate (+ 32: chain) per batch
+};
+
+// Folds the candidates [f0, f0 + nf) accepted last round into the rows'
+// state, then tests the candidates from `cursor` on under both guesses.
+// Memory-bound: a round reads rows x window x D floats (32 MB at 2048 rows,
+// d = 128), so a wave issues all loads of a row's window before the first use.
+template <int D>
+__device__ void joint_tests(const JointArgs& j, const RowState& st, int rb0, int nr, int cursor, int n_eff, int f0,
+                            int nf, unsigned* sMax, int* sAny) {
+  constexpr int KD = D / 64, NB = kJointWindow / kCandBatch;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int kind = lane >> 5, cq = (lane >> 1) & 15;
+  unsigned wmax[NB];
+  int wany[NB];
 #pragma unroll
-    for (int q = 0; q < RB; ++q) {
-      const int row = base + 4 * q;
-      const bool ok = row < r1;
-      const int rr = ok ? row : r0;
-      const float* rp =
-          pend >= 0 ? j.resid + (size_t)CKV_IDX((size_t)rr * j.max_cand + pend, (int64_t)j.total_rows * j.max_cand,
-                                                j.geo.dbg, 11) * j.D
-                    : nullptr;
-      const float* rt =
-          valid ? j.resid + (size_t)CKV_IDX((size_t)rr * j.max_cand + t, (int64_t)j.total_rows * j.max_cand,
-                                            j.geo.dbg, 11) * j.D
-                : nullptr;
+  for (int b = 0; b < NB; ++b) { wmax[b] = 0u; wany[b] = 0; }
+  for (int r = wave; r < nr; r += kJW) {
+    const int row = rb0 + r;
+    // this row's candidates sit together: 32-bit offsets from the row's base
+    const size_t rbase = (size_t)CKV_IDX(row, j.total_rows, j.geo.dbg, 11) * j.max_cand;
+    const float* rrow = j.resid + rbase * D;
+    const float* arow = j.resA + rbase;
+    const int* crow = j.resC + rbase;
+    float tv[kJointWindow][KD];
 #pragma unroll
-      for (int k = 0; k < KD; ++k) {
-        const int d = lane + 64 * k;
-        const bool dk = d < j.D;
-        dv[q][k] = dk ? Din[(size_t)rr * j.D + d] : 0.f;
-        rv[q][k] = (dk && rp) ? rp[d] : 0.f;
-        tv[q][k] = (dk && rt) ? rt[d] : 0.f;
-      }
-      Acur[q] = Ain[rr];
-      Ccur[q] = Cin[rr];
-      if (pend >= 0) {
-        Acur[q] += j.resA[(size_t)rr * j.max_cand + pend];
-        Ccur[q] += j.resC[(size_t)rr * j.max_cand + pend];
-      }
-      At[q] = valid ? j.resA[(size_t)rr * j.max_cand + t] : 0.f;
-      Ct[q] = valid ? j.resC[(size_t)rr * j.max_cand + t] : 0;
-      on[q] = rs.onorm[rr];
-      int c = 0;
-      for (int sl = 0; sl < j.n_vis_slices; ++sl) c += j.nvis_part[(rr % j.W) * j.n_vis_slices + sl];
-      nv[q] = c;
+    for (int c = 0; c < kJointWindow; ++c) {
+      const int t = min(cursor + c, n_eff - 1);
+#pragma unroll
+      for (int k = 0; k < KD; ++k) tv[c][k] = rrow[t * D + lane + 64 * k];
     }
+    const int tl = min(cursor + (lane & 31), n_eff - 1);
+    const float aw = arow[tl];
+    const int cw = crow[tl];
+    float dv[KD];
 #pragma unroll
-    for (int q = 0; q < RB; ++q) {
-      const int row = base + 4 * q;
-      if (row >= r1) continue;
-      float n2 = 0.f;
+    for (int k = 0; k < KD; ++k) dv[k] = st.D[r * D + lane + 64 * k];
+    float Ac = st.A[r];
+    int Cc = st.C[r];
+    if (nf > 0) {
+      for (int f = 0; f < nf; f += 8) {
+        float fv[8][KD], fa[8];
+        int fc[8];
 #pragma unroll
-      for (int k = 0; k < KD; ++k) {
-        const int d = lane + 64 * k;
-        if (d < j.D) {
-          const float x = dv[q][k] + rv[q][k];
-          if (jx == 0) Dout[(size_t)row * j.D + d] = x;
-          const float y = x + tv[q][k];
-          n2 += y * y;
+        for (int q = 0; q < 8; ++q) {
+          const int t = f0 + min(f + q, nf - 1);
+#pragma unroll
+          for (int k = 0; k < KD; ++k) fv[q][k] = rrow[t * D + lane + 64 * k];
+          fa[q] = arow[t];
+          fc[q] = crow[t];
         }
-      }
-      if (jx == 0 && lane == 0) { Aout[row] = Acur[q]; Cout[row] = Ccur[q]; }
-      if (!valid) continue;
 #pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) n2 += __shfl_xor(n2, off, 64);
-      const float Au = Acur[q] + At[q];
-      const int Cu = Ccur[q] + Ct[q];
-      float ratio = 0.f;
-      if (Cu > 0) {
-        const float keep = 1.f - Au;
-        if (Cu >= nv[q]) {
-          ratio = INFINITY;
-        } else if (Au > kJointFixA) {
-          // recomputed by definition after the round's tests
-          if (lane == 0) {
-            const int slot = atomicAdd(&j.ctrl[kFixN], 1);
-            if (slot < j.window * j.total_rows) store_pair(j.fix_list + 2 * slot, make_int2(jx, row));
+        for (int q = 0; q < 8; ++q)
+          if (f + q < nf) {
+#pragma unroll
+            for (int k = 0; k < KD; ++k) dv[k] += fv[q][k];
+            Ac += fa[q];
+            Cc += fc[q];
           }
-        } else if (on[q] > 0.f) {
-          ratio = sqrtf(n2) / (keep * on[q]);
-        } else {
-          ratio = n2 > 0.f ? INFINITY : 0.f;
-        }
       }
-      wmax = fmaxf(wmax, ratio);
+#pragma unroll
+      for (int k = 0; k < KD; ++k) st.D[r * D + lane + 64 * k] = dv[k];
+      st.A[r] = Ac;
+      st.C[r] = Cc;
+    }
+    const float on = st.onorm[r];
+    const int nv = st.nvis[r];
+    // chain sums of the masses and counts: lane c holds them through candidate c
+    float run = Ac, preA = 0.f;
+    int crun = Cc, preC = 0;
+#pragma unroll
+    for (int c = 0; c < kJointWindow; ++c) {
+      run += __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(aw), c));
+      crun += __builtin_amdgcn_readlane(cw, c);
+      preA = lane == c ? run : preA;
+      preC = lane == c ? crun : preC;
+    }
+    float pv[KD];
+#pragma unroll
+    for (int k = 0; k < KD; ++k) pv[k] = dv[k];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      float n2[2 * kCandBatch];   // squared norms: independent, then chain
+#pragma unroll
+      for (int q = 0; q < kCandBatch; ++q) {
+        float x2 = 0.f, y2 = 0.f;
+#pragma unroll
+        for (int k = 0; k < KD; ++k) {
+          const float x = dv[k] + tv[kCandBatch * b + q][k];
+          x2 = __builtin_fmaf(x, x, x2);
+          pv[k] += tv[kCandBatch * b + q][k];
+          y2 = __builtin_fmaf(pv[k], pv[k], y2);
+        }
+        n2[q] = x2;
+        n2[kCandBatch + q] = y2;
+      }
+      const float s = reduce_scatter32(n2, lane);
+      const int c = kCandBatch * b + cq;
+      // (every lane takes both exchanges: a lane reads nothing from a lane that sits one out)
+      const float A_i = Ac + __shfl(aw, c, 64), A_c = __shfl(preA, c, 64);
+      const int C_i = Cc + __shfl(cw, c, 64), C_c = __shfl(preC, c, 64);
+      const float Au = kind ? A_c : A_i;
+      const int Cu = kind ? C_c : C_i;
+      float ratio = 0.f;
+      bool fix = false;
+      if (cursor + c < n_eff && Cu > 0) {
+        if (Cu >= nv) ratio = INFINITY;
+        else if (Au > kJointFixA) fix = true;   // recomputed by definition
+        else if (on > 0.f) ratio = sqrtf(s) / ((1.f - Au) * on);
+        else ratio = s > 0.f ? INFINITY : 0.f;
+      }
+      st.fix[2 * r + b] = __ballot(fix && !(lane & 1));
+      if (ratio > 0.f) wmax[b] = max(wmax[b], __float_as_uint(ratio));
+      wany[b] |= fix ? 1 : 0;
     }
   }
-  if (valid && lane == 0) atomicMax(smax, __float_as_uint(wmax));
+  if (!(lane & 1)) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int w = 32 * kind + kCandBatch * b + cq;
+      if (wmax[b]) atomicMax(&sMax[w], wmax[b]);
+      if (wany[b]) sAny[w] = 1;
+    }
+  }
+}
+
+// The last workgroup of a round: maxima over the workgroups' words (bit 31:
+// some row of the workgroup left the pair to the fix-up), then the decision.
+// Two candidates' words per thread and load, every load issued at once.
+__device__ void joint_decide(const JointArgs& j, int cursor, int n_eff, int round, unsigned* sRed, int* sRedAny) {
+  constexpr int kGrp = kJT / 32, kPer = kJointBlocksMax / kGrp;
+  const int tid = threadIdx.x;
+  if (tid < 64) {
+    sRed[tid] = 0u;
+    sRedAny[tid] = 0;
+  }
   __syncthreads();
-  if (threadIdx.x == 0 && valid) atomicMax(&j.rbuf[jx], *smax);
+  {
+    const int w = tid & 31, grp = tid >> 5;
+    const unsigned long long* src = reinterpret_cast<const unsigned long long*>(j.bmax);
+    unsigned long long v[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int b = grp + kGrp * q;
+      v[q] = b < (int)gridDim.x ? ld_agent(&src[(size_t)b * 32 + w]) : 0ull;
+    }
+    unsigned m0 = 0u, m1 = 0u, any = 0u;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const unsigned lo = (unsigned)v[q], hi = (unsigned)(v[q] >> 32);
+      m0 = max(m0, lo & 0x7fffffffu);
+      m1 = max(m1, hi & 0x7fffffffu);
+      any |= (lo >> 31) | ((hi >> 31) << 1);
+    }
+    if (m0) atomicMax(&sRed[2 * w], m0);
+    if (m1) atomicMax(&sRed[2 * w + 1], m1);
+    if (any & 1u) sRedAny[2 * w] = 1;
+    if (any & 2u) sRedAny[2 * w + 1] = 1;
+  }
   __syncthreads();
+  if (tid >= 64) return;
+  const int c = tid & 31, t = cursor + c;
+  const float r = __uint_as_float(sRed[tid]);
+  const bool any = sRedAny[tid] != 0, valid = t < n_eff;
+  const unsigned long long bp = __ballot(valid && (j.accept_all || (r <= j.tau && !any)));
+  const unsigned long long bf = __ballot(valid && !j.accept_all && r > j.tau);
+  const unsigned long long ba = __ballot(any);
+  auto ones = [](unsigned x) { return x == 0xffffffffu ? 32 : __ffs(~x) - 1; };   // trailing ones
+  const unsigned pass_c = (unsigned)(bp >> 32), fail_c = (unsigned)(bf >> 32);
+  const unsigned pass_i = (unsigned)bp, fail_i = (unsigned)bf;
+  const int m = ones(pass_c);
+  const bool chain = m > 0;
+  const int n = chain ? m : ones(fail_i);
+  const bool extra = n < 32 && (((chain ? fail_c : pass_i) >> n) & 1u);
+  const bool resolve = n == 0 && !extra;
+  const int dec = n + (extra ? 1 : 0);
+  const unsigned decided = dec >= 32 ? 0xffffffffu : (1u << dec) - 1u;
+  const bool defer = j.want_union && ((unsigned)(chain ? ba >> 32 : ba) & decided) != 0u;
+  const bool mine = (tid >> 5) == (chain ? 1 : 0);   // the lanes that hold the chosen guess
+  if (mine && (c < dec || (resolve && c == 0))) st_agent(&j.ur[t], r);
+  if (mine && c < dec && (chain ? c < n : c == n)) {
+    st_agent(&j.accepted[t], (uint8_t)1);
+    const int ap = j.cand[t];
+    if (ap >= 0 && ap < j.n_pages) st_agent(&j.acc_t[ap], t);
+  }
+  if (tid == 0) {
+    unsigned p = (chain ? kDecChain : 0u) | (unsigned)n << 1 | (extra ? kDecExtra : 0u) |
+                 (resolve ? kDecResolve : 0u) | (defer ? kDecDefer : 0u);
+    // empty the list first unless it has room for a whole round's pairs
+    if ((defer || resolve) && ld_agent(&j.ctrl[kFixN]) > kJointWindow * j.total_rows) p |= kDecFlush;
+    st_agent(reinterpret_cast<unsigned long long*>(j.ctrl + kWord), (unsigned long long)round << 32 | p);
+  }
 }
 
-// Block 0, thread 0, after a round's tests: the first candidate in order
-// whose union maximum passes is accepted, the ones before it are rejected;
-// the cursor moves past the decided candidates and the accepted one becomes
-// the pending residual that the next round folds into the state.
-__device__ void decide_round(const JointArgs& j, int cursor, int n_eff) {
-  int cur = cursor, acc = -1;
-  for (int k = 0; k < j.window; ++k) {
-    const int tt = cursor + k;
-    if (tt >= n_eff) break;
-    const float r = __uint_as_float(__hip_atomic_load(&j.rbuf[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    if (j.union_R) j.union_R[tt] = r;
-    cur = tt + 1;
-    if (r <= j.tau || j.accept_all) {
-      j.accepted[tt] = 1;
-      acc = tt;
-      *j.n_accepted += 1;
-      const int ap = j.cand[tt];
-      if (ap >= 0 && ap < j.n_pages) __hip_atomic_store(&j.in_acc[ap], (uint8_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      break;
+// Lists the fix-up pairs of the candidates in the masks (bits as in
+// RowState::fix) for this wave's rows.
+__device__ void joint_append(const JointArgs& j, const RowState& st, int rb0, int nr, int cursor,
+                             unsigned long long mask0, unsigned long long mask1) {
+  const int lane = threadIdx.x & 63;
+  for (int r = threadIdx.x >> 6; r < nr; r += kJW) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const unsigned long long m = st.fix[2 * r + b] & (b ? mask1 : mask0);
+      if ((m >> lane) & 1ull) {
+        const int slot = __hip_atomic_fetch_add(&j.ctrl[kFixN], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (slot < j.fix_cap) store_pair(j.fix_list + 2 * slot, make_int2(cursor + kCandBatch * b + ((lane >> 1) & 15), rb0 + r));
+      }
     }
   }
-  for (int k = 0; k < j.window; ++k) __hip_atomic_store(&j.rbuf[k], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __hip_atomic_store(&j.ctrl[kFixN], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __hip_atomic_store(&j.ctrl[kCursor], cur, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __hip_atomic_store(&j.ctrl[kPending], acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The decision of decide_round from per-candidate maxima held in LDS (the
-// owned-row form); the global maxima are cleared for the next round.
-constexpr int kTargetBlocksMax = 256;   // workgroups of the owned-row form at most
-__device__ void decide_round_lds(const JointArgs& j, const unsigned int* sMax, int cursor, int n_eff) {
-  int cur = cursor, acc = -1;
-  for (int k = 0; k < j.window; ++k) {
-    const int tt = cursor + k;
-    if (tt >= n_eff) break;
-    const float r = __uint_as_float(sMax[k]);
-    if (j.union_R) j.union_R[tt] = r;
-    cur = tt + 1;
-    if (r <= j.tau || j.accept_all) {
-      j.accepted[tt] = 1;
-      acc = tt;
-      *j.n_accepted += 1;
-      const int ap = j.cand[tt];
-      if (ap >= 0 && ap < j.n_pages) __hip_atomic_store(&j.in_acc[ap], (uint8_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      break;
-    }
-  }
-  for (int k = 0; k < j.window; ++k) __hip_atomic_store(&j.rbuf[k], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __hip_atomic_store(&j.ctrl[kFixN], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __hip_atomic_store(&j.ctrl[kCursor], cur, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __hip_atomic_store(&j.ctrl[kPending], acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Fix-up of listed pairs e0 .. e0 + np - 1, `parts` items per pair: item
-// (e, part) sums w_i and w_i v_i over its slice of the row's tokens that are
-// visible and outside the union (accepted pages and the candidate's page),
-// with w_i = 2^(x_i - lse) <= 1, and writes the (D + 1) sums to fpart.
+// Fix-up of listed pairs e0 .. e0 + np - 1, one item per pair and `seg`
+// tokens of its row: sums w_i and w_i v_i over the tokens that are visible
+// and outside the union (the candidate's page and the pages accepted before
+// it), with w_i = 2^(x_i - lse) <= 1, and writes the (D + 1) sums to fpart.
 // Thread layout: D / 8 threads per token (16 bytes of its key and value
-// each), 256 / (D / 8) tokens per round.
+// each); the loads of UNR token rounds are in flight together, and the
+// union's tokens of the segment are marked in LDS once per item.
 template <int D, bool PG>
-__device__ void joint_fix_partial(const JointArgs& j, int cursor, int e0, int np, int parts, float* sacc) {
-  constexpr int TPR = D / 8, RPR = 256 / TPR;
+__device__ void joint_fix_partial(const JointArgs& j, int e0, int np, int seg, int parts, float* sacc,
+                                  uint8_t* sMask) {
+  constexpr int TPR = D / 8, RPR = kJT / TPR, UNR = 4;
   const AttnGeom& a = j.geo;
   const int tid = threadIdx.x, c = tid % TPR, r = tid / TPR;
   for (int item = blockIdx.x; item < np * parts; item += gridDim.x) {
-    const int e = e0 + item / parts, part = item % parts;
+    // consecutive items share the segment, so pairs of one head meet in the caches
+    const int e = e0 + item % np, part = item / np;
     const int2 ent = load_pair(j.fix_list + 2 * e);
     const int rg = (int)CKV_IDX(ent.y, j.total_rows, j.geo.dbg, 12);
-    const int cp = j.cand[CKV_IDX(cursor + ent.x, j.max_cand, j.geo.dbg, 13)];   // the candidate's page
+    const int t_c = (int)CKV_IDX(ent.x, j.max_cand, j.geo.dbg, 13);
+    const int cp = j.cand[t_c];   // the candidate's page
     const int h = rg / a.W, p = rg % a.W, g = h / a.group;
     const int qp = a.qpos[p];
     const float ref = j.lse[rg] * kLog2e;
-    const int seg = ((a.S + parts - 1) / parts + RPR - 1) / RPR * RPR;
     const int a0 = part * seg, a1 = min(a.S, a0 + seg);
     const uint16_t* kh = a.k + (int64_t)g * a.kv_head_stride;
     const uint16_t* vh = a.v + (int64_t)g * a.kv_head_stride;
     const u32x4 qc = ldg_u4(a.q + (int64_t)h * a.q_head_stride + (int64_t)p * a.q_row_stride + 8 * c);
-    float qv[8];
+    u32x4 kc[UNR], vc[UNR];
+    int pv[UNR];
+    auto load_round = [&](int b0) {
 #pragma unroll
-    for (int m = 0; m < 8; ++m) qv[m] = bf16_bits_to_float(chunk_elem(qc, m));
-    float acc[8];
-#pragma unroll
-    for (int m = 0; m < 8; ++m) acc[m] = 0.f;
-    float lacc = 0.f;
-    // first page whose end lies past this thread's first token
-    int pp = 0;
-    {
-      int lo = 0, hi = j.n_pages;
-      const int t0 = a0 + r;
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (j.pstart[mid] + j.plen[mid] <= t0) lo = mid + 1;
-        else hi = mid;
+      for (int u = 0; u < UNR; ++u) {
+        const int tt = min(b0 + u * RPR + r, a1 - 1);
+        const int64_t row = PG ? (int64_t)min((uint32_t)a.slot[tt], a.pool_last) : tt;
+        kc[u] = ldg_u4(kh + row * a.kv_tok_stride + 8 * c);
+        vc[u] = ldg_u4(vh + row * a.kv_tok_stride + 8 * c);
+        pv[u] = ldg_i32(a.pos + tt);
       }
-      pp = lo;
+    };
+    load_round(a0);
+    for (int i = tid; i < seg; i += kJT) sMask[i] = 0;
+    // pages are sorted and disjoint: the first one that reaches into the
+    // segment lies in [lo, hi], and at most `seg` more follow it
+    int lo = 0, hi = j.n_pages;
+    while (hi - lo > 1024) {
+      const int mid = (lo + hi) >> 1;
+      if (j.pstart[mid] + j.plen[mid] <= a0) lo = mid + 1;
+      else hi = mid;
     }
-    for (int b0 = a0; b0 < a1; b0 += RPR) {
-      const int t = b0 + r;
-      const int tt = min(t, a1 - 1);
-      const int64_t row = PG ? (int64_t)min((uint32_t)a.slot[tt], a.pool_last) : tt;
-      const u32x4 kc = ldg_u4(kh + row * a.kv_tok_stride + 8 * c);
-      const u32x4 vc = ldg_u4(vh + row * a.kv_tok_stride + 8 * c);
-      float x = 0.f;
+    __syncthreads();
+    for (int q = lo + tid; q < min(j.n_pages, hi + seg + 1); q += kJT) {
+      const int s0 = j.pstart[q], s1 = s0 + j.plen[q];
+      if (s0 < a1 && s1 > a0 && (q == cp || ld_agent(&j.acc_t[q]) < t_c))
+        for (int i = max(s0, a0); i < min(s1, a1); ++i) sMask[i - a0] = 1;
+    }
+    __syncthreads();
+    float qv[8], acc[8];
 #pragma unroll
-      for (int m = 0; m < 8; ++m) x = __builtin_fmaf(qv[m], bf16_bits_to_float(chunk_elem(kc, m)), x);
+    for (int m = 0; m < 8; ++m) {
+      qv[m] = bf16_bits_to_float(chunk_elem(qc, m));
+      acc[m] = 0.f;
+    }
+    float lacc = 0.f;
+    for (int b0 = a0; b0 < a1; b0 += UNR * RPR) {
+      if (b0 != a0) load_round(b0);
 #pragma unroll
-      for (int off = TPR / 2; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-      while (pp < j.n_pages && j.pstart[pp] + j.plen[pp] <= tt) ++pp;
-      const bool in_union = pp < j.n_pages && j.pstart[pp] <= tt && (pp == cp || __hip_atomic_load(&j.in_acc[pp], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0);
-      const bool keep = t < a1 && ldg_i32(a.pos + tt) <= qp && !in_union;
-      const float w = keep ? __builtin_amdgcn_exp2f(__builtin_fmaf(x, a.sl2, -ref)) : 0.f;
+      for (int u = 0; u < UNR; ++u) {
+        const int t = b0 + u * RPR + r;
+        float x = 0.f;
 #pragma unroll
-      for (int m = 0; m < 8; ++m) acc[m] = __builtin_fmaf(w, bf16_bits_to_float(chunk_elem(vc, m)), acc[m]);
-      if (c == 0) lacc += w;
+        for (int m = 0; m < 8; ++m) x = __builtin_fmaf(qv[m], bf16_bits_to_float(chunk_elem(kc[u], m)), x);
+#pragma unroll
+        for (int off = TPR / 2; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
+        const bool keep = t < a1 && pv[u] <= qp && !sMask[min(t, a1 - 1) - a0];
+        const float w = keep ? __builtin_amdgcn_exp2f(__builtin_fmaf(x, a.sl2, -ref)) : 0.f;
+#pragma unroll
+        for (int m = 0; m < 8; ++m) acc[m] = __builtin_fmaf(w, bf16_bits_to_float(chunk_elem(vc[u], m)), acc[m]);
+        if (c == 0) lacc += w;
+      }
     }
 #pragma unroll
     for (int m = 0; m < 8; ++m) sacc[r * (D + 1) + 8 * c + m] = acc[m];
@@ -347,92 +463,126 @@ __device__ void joint_fix_partial(const JointArgs& j, int cursor, int e0, int np
     __syncthreads();
     // the item's sums: token rows added in order
     float* out = j.fpart + ((size_t)(e - e0) * parts + part) * (D + 1);
-    for (int i = tid; i <= D; i += 256) {
+    for (int i = tid; i <= D; i += kJT) {
       float v = 0.f;
+#pragma unroll 8
       for (int k = 0; k < RPR; ++k) v += sacc[k * (D + 1) + i];
-      out[i] = v;
+      st_agent(out + i, v);
     }
     __syncthreads();
   }
 }
 
-// One wave per listed pair: parts added in order, o' = sum w v / sum w and
-// ||o - o'|| / ||o|| raised into the candidate's round maximum.
+// One workgroup per listed pair: each wave adds its share of the parts in
+// order, the waves' sums are added in order, o' = sum w v / sum w, and
+// ||o - o'|| / ||o|| is raised into the candidate's union effect.
 template <int D>
-__device__ void joint_fix_final(const JointArgs& j, int e0, int np, int parts) {
-  const int lane = threadIdx.x & 63;
-  for (int e = e0 + blockIdx.x * 4 + (threadIdx.x >> 6); e < e0 + np; e += gridDim.x * 4) {
+__device__ void joint_fix_final(const JointArgs& j, int e0, int np, int parts, float* sacc) {
+  constexpr int KD = D / 64;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int per = (parts + kJW - 1) / kJW;
+  for (int e = e0 + blockIdx.x; e < e0 + np; e += gridDim.x) {
     const int2 ent = load_pair(j.fix_list + 2 * e);
-    const int rg = ent.y;
     const float* fp = j.fpart + (size_t)(e - e0) * parts * (D + 1);
-    float num[D / 64], den = 0.f;
+    float num[KD], den = 0.f;
 #pragma unroll
-    for (int m = 0; m < D / 64; ++m) num[m] = 0.f;
-    for (int part = 0; part < parts; ++part) {
+    for (int m = 0; m < KD; ++m) num[m] = 0.f;
+    const int p1 = min(parts, (wave + 1) * per);
+#pragma unroll 8
+    for (int part = wave * per; part < p1; ++part) {
 #pragma unroll
-      for (int m = 0; m < D / 64; ++m) num[m] += fp[part * (D + 1) + lane + 64 * m];
-      den += fp[part * (D + 1) + D];
-    }
-    float dd = 0.f, oo = 0.f;
-#pragma unroll
-    for (int m = 0; m < D / 64; ++m) {
-      const float ov = j.o[(size_t)rg * D + lane + 64 * m];
-      const float od = den > 0.f ? num[m] / den : 0.f;
-      dd += (ov - od) * (ov - od);
-      oo += ov * ov;
+      for (int m = 0; m < KD; ++m) num[m] += ld_agent(fp + (size_t)part * (D + 1) + lane + 64 * m);
+      den += ld_agent(fp + (size_t)part * (D + 1) + D);
     }
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      dd += __shfl_xor(dd, off, 64);
-      oo += __shfl_xor(oo, off, 64);
+    for (int m = 0; m < KD; ++m) sacc[wave * (D + 1) + lane + 64 * m] = num[m];
+    if (lane == 0) sacc[wave * (D + 1) + D] = den;
+    __syncthreads();
+    if (wave == 0) {
+      float dd = 0.f, oo = 0.f, ds = 0.f;
+#pragma unroll
+      for (int k = 0; k < kJW; ++k) ds += sacc[k * (D + 1) + D];
+#pragma unroll
+      for (int m = 0; m < KD; ++m) {
+        float ns = 0.f;
+#pragma unroll
+        for (int k = 0; k < kJW; ++k) ns += sacc[k * (D + 1) + lane + 64 * m];
+        const float ov = j.o[(size_t)ent.y * D + lane + 64 * m];
+        const float od = ds > 0.f ? ns / ds : 0.f;
+        dd += (ov - od) * (ov - od);
+        oo += ov * ov;
+      }
+#pragma unroll
+      for (int off = 32; off >= 1; off >>= 1) {
+        dd += __shfl_xor(dd, off, 64);
+        oo += __shfl_xor(oo, off, 64);
+      }
+      if (lane == 0) {
+        float ratio;
+        if (!(ds > 0.f)) ratio = INFINITY;
+        else if (oo > 0.f) ratio = sqrtf(dd) / sqrtf(oo);
+        else ratio = dd > 0.f ? INFINITY : 0.f;
+        __hip_atomic_fetch_max(reinterpret_cast<unsigned*>(&j.ur[ent.x]), __float_as_uint(ratio), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+      }
     }
-    if (lane == 0) {
-      float ratio;
-      if (!(den > 0.f)) ratio = INFINITY;
-      else if (oo > 0.f) ratio = sqrtf(dd) / sqrtf(oo);
-      else ratio = dd > 0.f ? INFINITY : 0.f;
-      atomicMax(&j.rbuf[ent.x], __float_as_uint(ratio));
-    }
+    __syncthreads();
   }
 }
 
-__global__ __launch_bounds__(256) void joint_persistent(JointArgs j, RowStats rs) {
-  __shared__ unsigned int smax;
-  __shared__ int s_ok, s_part[4];
-  __shared__ float sacc[32 * 65];    // fix-up: RPR token rows x (D + 1) sums (16 x 129 for D = 128)
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t gsz = (size_t)gridDim.x * blockDim.x;
+// Recomputes every listed pair and empties the list (in every workgroup; the
+// first barrier publishes the workgroups' appends).
+template <int D>
+__device__ bool joint_flush(const JointArgs& j, int& target, int* s_flag, float* sacc, uint8_t* sMask) {
+  target += gridDim.x;
+  if (!joint_barrier(j.ctrl, target, j.barrier_ticks, s_flag)) return false;
+  const int n = min(ld_agent(&j.ctrl[kFixN]), j.fix_cap);
+  if (n == 0) return true;   // the same in every block
+  const int S = j.geo.S;
+  int seg = 256;             // short segments while the items are few
+  while (seg < kFixSegMax && (int64_t)n * ((S + seg - 1) / seg) > 32 * kJointBlocksMax) seg *= 2;
+  const int parts = (S + seg - 1) / seg;
+  const int npc = max(1, kJointFixItems / parts);   // pairs whose partial sums fit the workspace
+  for (int e0 = 0; e0 < n; e0 += npc) {
+    const int np = min(npc, n - e0);
+    if (j.geo.slot) joint_fix_partial<D, true>(j, e0, np, seg, parts, sacc, sMask);
+    else joint_fix_partial<D, false>(j, e0, np, seg, parts, sacc, sMask);
+    target += gridDim.x;
+    if (!joint_barrier(j.ctrl, target, j.barrier_ticks, s_flag)) return false;
+    if (e0 + npc >= n && blockIdx.x == 0 && threadIdx.x == 0) st_agent(&j.ctrl[kFixN], 0);   // read by all above
+    joint_fix_final<D>(j, e0, np, parts, sacc);
+    target += gridDim.x;
+    if (!joint_barrier(j.ctrl, target, j.barrier_ticks, s_flag)) return false;
+  }
+  return true;
+}
+
+// LDS: the rows' state is kept in LDS (nr <= kRowsOwnedMax)
+template <int D, bool LDS>
+__global__ __launch_bounds__(kJT) void joint_rounds(JointArgs j) {
+  constexpr int KD = D / 64, NR = LDS ? kRowsOwnedMax : 1;
+  __shared__ float sD[LDS ? NR * D : 1];
+  __shared__ float sA[NR], sOn[NR];
+  __shared__ int sC[NR], sNv[NR];
+  __shared__ unsigned long long sFix[2 * NR];
+  __shared__ unsigned sMax[64], sRed[64];
+  __shared__ int sAny[64], sRedAny[64];
+  __shared__ unsigned long long s_word;
+  __shared__ int s_flag, s_part[kJW];
+  __shared__ float sacc[(kJT / (D / 8)) * (D + 1)];   // fix-up: token rows x (D + 1) sums
+  __shared__ uint8_t sMask[kFixSegMax];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const size_t gid = (size_t)blockIdx.x * kJT + tid, gsz = (size_t)gridDim.x * kJT;
   const int n_eff = min(min(*j.n_cand, j.max_cand), j.test_cap);
-  // phase 0: outputs, state, ||o_p|| and visible-token counts
+  // outputs; every word that another workgroup may write later goes through
+  // agent-scope stores, so the first barrier needs no fence either
   for (size_t i = gid; i < (size_t)j.max_cand; i += gsz) {
-    j.accepted[i] = 0;
-    if (j.union_R) j.union_R[i] = __builtin_nanf("");
+    st_agent(&j.accepted[i], (uint8_t)0);
+    st_agent(&j.ur[i], __builtin_nanf(""));
   }
-  if (gid == 0) *j.n_accepted = 0;
+  if (gid == 0) st_agent(j.n_accepted, 0);
   if (n_eff <= 0) return;              // nothing to test: the same in every block
-  for (size_t i = gid; i < (size_t)j.total_rows * j.D; i += gsz) j.Dstate[i] = 0.f;
-  for (size_t i = gid; i < (size_t)j.total_rows; i += gsz) { j.Astate[i] = 0.f; j.Cstate[i] = 0; }
-  for (size_t i = gid; i < (size_t)j.window; i += gsz) j.rbuf[i] = 0u;
-  for (size_t i = gid; i < (size_t)j.n_pages; i += gsz) j.in_acc[i] = 0;
-  if (gid == 0) {
-    j.ctrl[kCursor] = 0;
-    j.ctrl[kPending] = -1;
-    j.ctrl[kParity] = 0;
-  }
-  for (int row = blockIdx.x * 4 + wave; row < j.total_rows; row += gridDim.x * 4) {
-    float n2 = 0.f;
-    for (int d = lane; d < j.D; d += 64) {
-      const float v = j.o[(size_t)row * j.D + d];
-      n2 += v * v;
-    }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) n2 += __shfl_xor(n2, off, 64);
-    if (lane == 0) {
-      rs.onorm[row] = sqrtf(n2);
-      if (!(n2 <= 3.4e38f) || !(j.lse[row] < INFINITY)) latch_nonfinite(j.nonfinite);
-    }
-  }
+  for (size_t i = gid; i < (size_t)j.n_pages; i += gsz) st_agent(&j.acc_t[i], INT_MAX);
   // n_vis of window row p (shared by every query head): #{i : pos[i] <= qpos[p]},
   // one partial count per (row, token slice)
   for (int it = blockIdx.x; it < j.W * j.n_vis_slices; it += gridDim.x) {
@@ -440,373 +590,148 @@ __global__ __launch_bounds__(256) void joint_persistent(JointArgs j, RowStats rs
     const int qp = j.qpos[p];
     const int t0 = sl * kVisSlice, t1 = min(j.S, t0 + kVisSlice);
     int c = 0;
-    for (int i = t0 + (int)threadIdx.x; i < t1; i += 256) c += j.pos[i] <= qp ? 1 : 0;
+    for (int i = t0 + tid; i < t1; i += kJT) c += j.pos[i] <= qp ? 1 : 0;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off, 64);
     if (lane == 0) s_part[wave] = c;
     __syncthreads();
-    if (threadIdx.x == 0) j.nvis_part[it] = s_part[0] + s_part[1] + s_part[2] + s_part[3];
+    if (tid == 0) {
+      int s = 0;
+      for (int w = 0; w < kJW; ++w) s += s_part[w];
+      st_agent(&j.nvis_part[it], s);
+    }
     __syncthreads();
   }
-  int target = gridDim.x;
-  if (!grid_barrier(j.ctrl, target, j.barrier_ticks, &s_ok)) {
-    if (threadIdx.x == 0) *j.n_accepted = -1;
-    return;
-  }
-  const int n_rb = (j.total_rows + j.rows_per_block - 1) / j.rows_per_block;
-  const int items = j.window * n_rb;
-  // every round decides at least one candidate: n_eff rounds suffice
-  for (int round = 0; round < n_eff; ++round) {
-    const int cursor = __hip_atomic_load(&j.ctrl[kCursor], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int pend = __hip_atomic_load(&j.ctrl[kPending], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int par = __hip_atomic_load(&j.ctrl[kParity], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (cursor >= n_eff) break;               // the same decision in every block
-    for (int it = blockIdx.x; it < items; it += gridDim.x)
-      joint_item(j, rs, it / n_rb, it % n_rb, cursor, pend, par, n_eff, &smax);
-    target += gridDim.x;
-    if (!grid_barrier(j.ctrl, target, j.barrier_ticks, &s_ok)) {
-      if (threadIdx.x == 0) *j.n_accepted = -1;
-      return;
-    }
-    // listed pairs, recomputed by definition in chunks that fit the
-    // workspace (the same count and chunks in every block)
-    const int nfix = min(__hip_atomic_load(&j.ctrl[kFixN], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
-                         j.window * j.total_rows);
-    for (int e0 = 0; e0 < nfix; e0 += kJointFixItems) {
-      const int np = min(nfix - e0, kJointFixItems);
-      const int parts = max(1, min(kJointFixParts, kJointFixItems / np));
-      const bool pg = j.geo.slot != nullptr;
-      if (j.D == 128) {
-        if (pg) joint_fix_partial<128, true>(j, cursor, e0, np, parts, sacc);
-        else joint_fix_partial<128, false>(j, cursor, e0, np, parts, sacc);
-      } else {
-        if (pg) joint_fix_partial<64, true>(j, cursor, e0, np, parts, sacc);
-        else joint_fix_partial<64, false>(j, cursor, e0, np, parts, sacc);
-      }
-      target += gridDim.x;
-      if (!grid_barrier(j.ctrl, target, j.barrier_ticks, &s_ok)) {
-        if (threadIdx.x == 0) *j.n_accepted = -1;
-        return;
-      }
-      if (j.D == 128) joint_fix_final<128>(j, e0, np, parts);
-      else joint_fix_final<64>(j, e0, np, parts);
-      target += gridDim.x;
-      if (!grid_barrier(j.ctrl, target, j.barrier_ticks, &s_ok)) {
-        if (threadIdx.x == 0) *j.n_accepted = -1;
-        return;
-      }
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      decide_round(j, cursor, n_eff);
-      __hip_atomic_store(&j.ctrl[kParity], par ^ 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    target += gridDim.x;
-    if (!grid_barrier(j.ctrl, target, j.barrier_ticks, &s_ok)) {
-      if (threadIdx.x == 0) *j.n_accepted = -1;
-      return;
-    }
-  }
-}
-
-// Rows owned by workgroups: the fast form of the rounds.  Workgroup b owns
-// window rows [b * rpb, (b + 1) * rpb) for the whole call and keeps their
-// accumulated state (D, A_A, visible counts) in LDS, so a round touches
-// global memory only to read the tested candidates' residual rows and to
-// publish one maximum per candidate; nothing written to global memory has
-// to be made visible across workgroups except through atomics.  A wave
-// tests a row against up to 16 candidates with every load issued first.
-constexpr int kRowsOwnedMax = 64;   // rows a workgroup owns at most (host checks)
-constexpr int kCandBatch = 16;      // candidates whose residual rows are loaded together
-
-template <int D>
-__device__ void owned_round_tests(const JointArgs& j, float* sD, const float* sA, const int* sC,
-                                  const float* sOn, const int* sNv, unsigned int* sMax, int rb0, int nr,
-                                  int cursor, int n_eff) {
-  constexpr int KD = D / 64;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int r = wave; r < nr; r += 4) {
-    const int row = rb0 + r;
-    float dv[KD];
-#pragma unroll
-    for (int k = 0; k < KD; ++k) dv[k] = sD[r * D + lane + 64 * k];
-    const float Acur = sA[r], on = sOn[r];
-    const int Ccur = sC[r], nv = sNv[r];
-    for (int jb = 0; jb < j.window; jb += kCandBatch) {
-      float tv[kCandBatch][KD], tA[kCandBatch];
-      int tC[kCandBatch];
-      // this row's candidates sit together: 32-bit offsets from the row's base
-      const float* rrow = j.resid + (size_t)row * j.max_cand * D;
-      const float* arow = j.resA + (size_t)row * j.max_cand;
-      const int* crow = j.resC + (size_t)row * j.max_cand;
-#pragma unroll
-      for (int q = 0; q < kCandBatch; ++q) {
-        const int t = cursor + jb + q;
-        const bool valid = jb + q < j.window && t < n_eff;
-        const int tt = valid ? t : cursor;
-#pragma unroll
-        for (int k = 0; k < KD; ++k) tv[q][k] = rrow[tt * D + lane + 64 * k];
-        tA[q] = arow[tt];
-        tC[q] = crow[tt];
-        if (!valid) {
-#pragma unroll
-          for (int k = 0; k < KD; ++k) tv[q][k] = 0.f;
-          tA[q] = 0.f;
-          tC[q] = 0;
-        }
-      }
-      // squared norms of the batch's unions, reduced across the wave
-      // together (the batch's exchanges overlap instead of chaining)
-      float n2v[kCandBatch];
-#pragma unroll
-      for (int q = 0; q < kCandBatch; ++q) {
-        float n2 = 0.f;
-#pragma unroll
-        for (int k = 0; k < KD; ++k) {
-          const float y = dv[k] + tv[q][k];
-          n2 += y * y;
-        }
-        n2v[q] = n2;
-      }
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1)
-#pragma unroll
-        for (int q = 0; q < kCandBatch; ++q) n2v[q] += __shfl_xor(n2v[q], off, 64);
-#pragma unroll
-      for (int q = 0; q < kCandBatch; ++q) {
-        const int jx = jb + q;
-        if (jx >= j.window || cursor + jx >= n_eff) break;
-        const float n2 = n2v[q];
-        const float Au = Acur + tA[q];
-        const int Cu = Ccur + tC[q];
-        float ratio = 0.f;
-        if (Cu > 0) {
-          if (Cu >= nv) {
-            ratio = INFINITY;
-          } else if (Au > kJointFixA) {
-            // recomputed by definition after the round's tests
-            if (lane == 0) {
-              const int slot = atomicAdd(&j.ctrl[kFixN], 1);
-              if (slot < j.window * j.total_rows) store_pair(j.fix_list + 2 * slot, make_int2(jx, row));
-            }
-          } else if (on > 0.f) {
-            ratio = sqrtf(n2) / ((1.f - Au) * on);
-          } else {
-            ratio = n2 > 0.f ? INFINITY : 0.f;
-          }
-        }
-        if (lane == 0 && ratio > 0.f) atomicMax(&sMax[jx], __float_as_uint(ratio));
-      }
-    }
-  }
-}
-
-__global__ __launch_bounds__(256) void joint_owned(JointArgs j, RowStats rs) {
-  __shared__ float sD[kRowsOwnedMax * 128];
-  __shared__ float sA[kRowsOwnedMax], sOn[kRowsOwnedMax];
-  __shared__ int sC[kRowsOwnedMax], sNv[kRowsOwnedMax];
-  __shared__ unsigned int sMax[64];
-  __shared__ int s_ok, s_part[4];
-  __shared__ float sacc[32 * 65];    // fix-up: RPR token rows x (D + 1) sums
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t gsz = (size_t)gridDim.x * blockDim.x;
-  const int n_eff = min(min(*j.n_cand, j.max_cand), j.test_cap);
-  // phase 0: outputs, ||o_p|| and visible-token counts
-  for (size_t i = gid; i < (size_t)j.max_cand; i += gsz) {
-    j.accepted[i] = 0;
-    if (j.union_R) j.union_R[i] = __builtin_nanf("");
-  }
-  if (gid == 0) *j.n_accepted = 0;
-  if (n_eff <= 0) return;              // nothing to test: the same in every block
-  for (size_t i = gid; i < (size_t)j.window; i += gsz) j.rbuf[i] = 0u;
-  for (size_t i = gid; i < (size_t)j.n_pages; i += gsz) j.in_acc[i] = 0;
-  if (gid == 0) {
-    j.ctrl[kCursor] = 0;
-    j.ctrl[kPending] = -1;
-  }
-  for (int row = blockIdx.x * 4 + wave; row < j.total_rows; row += gridDim.x * 4) {
-    float n2 = 0.f;
-    for (int d = lane; d < j.D; d += 64) {
-      const float v = j.o[(size_t)row * j.D + d];
-      n2 += v * v;
-    }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) n2 += __shfl_xor(n2, off, 64);
-    if (lane == 0) {
-      rs.onorm[row] = sqrtf(n2);
-      if (!(n2 <= 3.4e38f) || !(j.lse[row] < INFINITY)) latch_nonfinite(j.nonfinite);
-    }
-  }
-  for (int it = blockIdx.x; it < j.W * j.n_vis_slices; it += gridDim.x) {
-    const int p = it / j.n_vis_slices, sl = it % j.n_vis_slices;
-    const int qp = j.qpos[p];
-    const int t0 = sl * kVisSlice, t1 = min(j.S, t0 + kVisSlice);
-    int c = 0;
-    for (int i = t0 + (int)threadIdx.x; i < t1; i += 256) c += j.pos[i] <= qp ? 1 : 0;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off, 64);
-    if (lane == 0) s_part[wave] = c;
-    __syncthreads();
-    if (threadIdx.x == 0) j.nvis_part[it] = s_part[0] + s_part[1] + s_part[2] + s_part[3];
-    __syncthreads();
-  }
-  int target = gridDim.x;
-  if (!grid_barrier(j.ctrl, target, j.barrier_ticks, &s_ok)) {
-    if (threadIdx.x == 0) *j.n_accepted = -1;
-    return;
-  }
-  // this workgroup's rows and their state
+  // this workgroup's rows: state and ||o_p||
   const int rpb = (j.total_rows + gridDim.x - 1) / gridDim.x;
   const int rb0 = blockIdx.x * rpb;
   const int nr = max(0, min(rpb, j.total_rows - rb0));
-  for (int i = threadIdx.x; i < nr * j.D; i += 256) sD[i] = 0.f;
-  for (int r = threadIdx.x; r < nr; r += 256) {
+  RowState st;
+  if constexpr (LDS) st = RowState{sD, sA, sC, sOn, sNv, sFix};
+  else st = RowState{j.st_D + (size_t)rb0 * D, j.st_A + rb0, j.st_C + rb0, j.st_on + rb0, j.st_nv + rb0, j.st_fix + 2 * (size_t)rb0};
+  for (int r = wave; r < nr; r += kJW) {
     const int row = rb0 + r;
-    sA[r] = 0.f;
-    sC[r] = 0;
-    sOn[r] = rs.onorm[row];
+    float n2 = 0.f;
+#pragma unroll
+    for (int k = 0; k < KD; ++k) {
+      const float v = j.o[(size_t)row * D + lane + 64 * k];
+      n2 = __builtin_fmaf(v, v, n2);
+      st.D[r * D + lane + 64 * k] = 0.f;
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) n2 += __shfl_xor(n2, off, 64);
+    st.onorm[r] = sqrtf(n2);
+    st.A[r] = 0.f;
+    st.C[r] = 0;
+    if (lane == 0 && (!(n2 <= 3.4e38f) || !(j.lse[row] < INFINITY))) latch_nonfinite(j.nonfinite);
+  }
+  int target = gridDim.x;
+  auto give_up = [&] {
+    if (tid == 0) st_agent(j.n_accepted, -1);
+  };
+  if (!joint_barrier(j.ctrl, target, j.barrier_ticks, &s_flag)) return give_up();
+  for (int r = wave; r < nr; r += kJW) {
+    const int row = rb0 + r;
     int c = 0;
-    for (int q = 0; q < j.n_vis_slices; ++q) c += j.nvis_part[(row % j.W) * j.n_vis_slices + q];
-    sNv[r] = c;
+    for (int q = lane; q < j.n_vis_slices; q += 64) c += ld_agent(&j.nvis_part[(row % j.W) * j.n_vis_slices + q]);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off, 64);
+    st.nvis[r] = c;
   }
+  int cursor = 0, n_acc = 0, f0 = 0, nf = 0;
+  bool listed = false;
   // every round decides at least one candidate: n_eff rounds suffice
-  for (int round = 0; round < n_eff; ++round) {
-    const int cursor = __hip_atomic_load(&j.ctrl[kCursor], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int pend = __hip_atomic_load(&j.ctrl[kPending], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (cursor >= n_eff) break;               // the same decision in every block
-    // the candidate accepted last round joins this workgroup's rows' state
-    if (pend >= 0) {
-      // every load of the fold issued before the first add
-      constexpr int kFold = kRowsOwnedMax * 128 / 256;
-      float add[kFold];
-      const float* pbase = j.resid + ((size_t)rb0 * j.max_cand + pend) * j.D;
-      const int rstride = j.max_cand * j.D;
-#pragma unroll
-      for (int q = 0; q < kFold; ++q) {
-        const int i = threadIdx.x + 256 * q;
-        add[q] = i < nr * j.D ? pbase[(i / j.D) * rstride + i % j.D] : 0.f;
-      }
-      float aA = 0.f;
-      int aC = 0;
-      if ((int)threadIdx.x < nr) {
-        aA = j.resA[(size_t)(rb0 + threadIdx.x) * j.max_cand + pend];
-        aC = j.resC[(size_t)(rb0 + threadIdx.x) * j.max_cand + pend];
-      }
-#pragma unroll
-      for (int q = 0; q < kFold; ++q) {
-        const int i = threadIdx.x + 256 * q;
-        if (i < nr * j.D) sD[i] += add[q];
-      }
-      if ((int)threadIdx.x < nr) {
-        sA[threadIdx.x] += aA;
-        sC[threadIdx.x] += aC;
-      }
+  for (int round = 1; cursor < n_eff; ++round) {
+    if (tid < 64) {
+      sMax[tid] = 0u;
+      sAny[tid] = 0;
     }
-    for (int i = threadIdx.x; i < j.window; i += 256) sMax[i] = 0u;
     __syncthreads();
-    if (j.D == 128) owned_round_tests<128>(j, sD, sA, sC, sOn, sNv, sMax, rb0, nr, cursor, n_eff);
-    else owned_round_tests<64>(j, sD, sA, sC, sOn, sNv, sMax, rb0, nr, cursor, n_eff);
+    joint_tests<D>(j, st, rb0, nr, cursor, n_eff, f0, nf, sMax, sAny);
     __syncthreads();
-    // this workgroup's maxima go to its own slots (no contended atomics);
-    // workgroup 0 reduces them after the barrier
-    for (int i = threadIdx.x; i < j.window; i += 256)
-      __hip_atomic_store(&j.bmax[(size_t)blockIdx.x * j.window + i], sMax[i], __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
+    // this workgroup's maxima go to its own words (no contended atomics)
+    if (tid < 64) st_agent(&j.bmax[(size_t)blockIdx.x * 64 + tid], sMax[tid] | (sAny[tid] ? 0x80000000u : 0u));
     target += gridDim.x;
-    if (!grid_barrier_nofence(j.ctrl, target, j.barrier_ticks, &s_ok)) {
-      if (threadIdx.x == 0) *j.n_accepted = -1;
-      return;
+    if (joint_arrive(j.ctrl, target, &s_flag)) joint_decide(j, cursor, n_eff, round, sRed, sRedAny);
+    __syncthreads();
+    const unsigned long long* word = reinterpret_cast<const unsigned long long*>(j.ctrl + kWord);
+    if (!joint_wait(j.ctrl, j.barrier_ticks, &s_flag, [&] {
+          s_word = ld_agent(word);
+          return (s_word >> 32) == (unsigned long long)round;
+        }))
+      return give_up();
+    const unsigned dec = (unsigned)s_word;
+    const bool chain = dec & kDecChain;
+    const int n = (dec >> 1) & 63, extra = (dec & kDecExtra) ? 1 : 0;
+    f0 = chain ? cursor : cursor + n;    // the candidates accepted in this round
+    nf = chain ? n : extra;
+    if ((dec & kDecFlush) && !joint_flush<D>(j, target, &s_flag, sacc, sMask)) return give_up();
+    if (dec & (kDecDefer | kDecResolve)) {
+      // candidates [0, nd) of the chosen guess, as bits of RowState::fix
+      const int nd = (dec & kDecResolve) ? 1 : n + extra;
+      auto bits = [&](int m) {
+        const unsigned long long b = m <= 0 ? 0ull : 0x55555555ull >> (32 - 2 * min(m, 16));
+        return chain ? b << 32 : b;
+      };
+      joint_append(j, st, rb0, nr, cursor, bits(nd), bits(nd - 16));
+      listed = true;
     }
-    // listed pairs, recomputed by definition in chunks that fit the
-    // workspace (the same count and chunks in every block)
-    const int nfix = min(__hip_atomic_load(&j.ctrl[kFixN], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
-                         j.window * j.total_rows);
-    for (int e0 = 0; e0 < nfix; e0 += kJointFixItems) {
-      const int np = min(nfix - e0, kJointFixItems);
-      const int parts = max(1, min(kJointFixParts, kJointFixItems / np));
-      const bool pg = j.geo.slot != nullptr;
-      if (j.D == 128) {
-        if (pg) joint_fix_partial<128, true>(j, cursor, e0, np, parts, sacc);
-        else joint_fix_partial<128, false>(j, cursor, e0, np, parts, sacc);
-      } else {
-        if (pg) joint_fix_partial<64, true>(j, cursor, e0, np, parts, sacc);
-        else joint_fix_partial<64, false>(j, cursor, e0, np, parts, sacc);
+    if (dec & kDecResolve) {
+      // the candidate at the cursor: its union effect is complete after a flush
+      if (!joint_flush<D>(j, target, &s_flag, sacc, sMask)) return give_up();
+      listed = false;
+      const bool pass = ld_agent(&j.ur[cursor]) <= j.tau;
+      f0 = cursor;
+      nf = pass ? 1 : 0;
+      if (pass && gid == 0) {
+        st_agent(&j.accepted[cursor], (uint8_t)1);
+        const int ap = j.cand[cursor];
+        if (ap >= 0 && ap < j.n_pages) st_agent(&j.acc_t[ap], cursor);
       }
-      target += gridDim.x;
-      if (!grid_barrier(j.ctrl, target, j.barrier_ticks, &s_ok)) {
-        if (threadIdx.x == 0) *j.n_accepted = -1;
-        return;
-      }
-      if (j.D == 128) joint_fix_final<128>(j, e0, np, parts);
-      else joint_fix_final<64>(j, e0, np, parts);
-      target += gridDim.x;
-      if (!grid_barrier(j.ctrl, target, j.barrier_ticks, &s_ok)) {
-        if (threadIdx.x == 0) *j.n_accepted = -1;
-        return;
-      }
+      cursor += 1;
+    } else {
+      cursor += n + extra;
     }
-    if (blockIdx.x == 0) {
-      // maxima over the workgroups' slots and the fix-up's maxima, every
-      // load issued at once; then the decision from LDS
-      for (int i = threadIdx.x; i < j.window; i += 256) sMax[i] = 0u;
-      __syncthreads();
-      {
-        constexpr int kPer = kTargetBlocksMax / 8;   // slots per thread: 8 threads per candidate
-        const int jx = threadIdx.x % 32, b0 = threadIdx.x / 32;
-        unsigned int v[kPer];
-#pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-          const int b = b0 + 8 * q;
-          v[q] = (jx < j.window && b < (int)gridDim.x)
-                     ? __hip_atomic_load(&j.bmax[(size_t)b * j.window + jx], __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_AGENT)
-                     : 0u;
-        }
-        unsigned int m = 0u;
-#pragma unroll
-        for (int q = 0; q < kPer; ++q) m = max(m, v[q]);
-        if (jx < j.window && b0 == 0)
-          m = max(m, __hip_atomic_load(&j.rbuf[jx], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        if (jx < j.window) atomicMax(&sMax[jx], m);
-      }
-      __syncthreads();
-      if (threadIdx.x == 0) decide_round_lds(j, sMax, cursor, n_eff);
-    }
-    target += gridDim.x;
-    if (!grid_barrier_nofence(j.ctrl, target, j.barrier_ticks, &s_ok)) {
-      if (threadIdx.x == 0) *j.n_accepted = -1;
-      return;
-    }
+    n_acc += nf;
   }
+  if (listed && !joint_flush<D>(j, target, &s_flag, sacc, sMask)) return give_up();
+  if (gid == 0 && ld_agent(&j.ctrl[kError]) == 0) st_agent(j.n_accepted, n_acc);
 }
 
 int joint_vis_slices(int S) { return (S + kVisSlice - 1) / kVisSlice; }
 
-hipError_t launch_joint_persistent(const JointArgs& j, int max_blocks, hipStream_t s) {
-  RowStats rs{nullptr, nullptr, const_cast<float*>(j.onorm), nullptr, nullptr, nullptr, nullptr};
-  const int n_rb = (j.total_rows + j.rows_per_block - 1) / j.rows_per_block;
+namespace {
+typedef void (*JointKernel)(JointArgs);
+JointKernel joint_kernel(int D, bool lds) {
+  if (D == 128) return lds ? joint_rounds<128, true> : joint_rounds<128, false>;
+  return lds ? joint_rounds<64, true> : joint_rounds<64, false>;
+}
+}  // namespace
+
+// rows a call's workgroups own at most when every workgroup is used; above
+// kRowsOwnedMax the rows' state lives in the caller's workspace
+bool joint_state_global(int total_rows) { return (total_rows + kJointBlocksMax - 1) / kJointBlocksMax > kRowsOwnedMax; }
+
+hipError_t launch_joint(const JointArgs& j, hipStream_t s) {
   // workgroups of each form that fit on the device at once (queried once per device)
-  static int resident[64][2];
+  static int resident[64][4];
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-  if (resident[dev][0] <= 0) {
-    int per_cu = 0, per_cu2 = 0, cus = 0;
-    if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, joint_persistent, 256, 0)) != hipSuccess) return e;
-    if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu2, joint_owned, 256, 0)) != hipSuccess) return e;
+  const bool lds = !joint_state_global(j.total_rows);
+  const JointKernel kern = joint_kernel(j.D, lds);
+  int& res = resident[dev][(j.D == 128 ? 2 : 0) + (lds ? 1 : 0)];
+  if (res <= 0) {
+    int per_cu = 0, cus = 0;
+    if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kJT, 0)) != hipSuccess) return e;
     if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-    resident[dev][0] = std::max(1, per_cu * cus);
-    resident[dev][1] = std::max(1, per_cu2 * cus);
+    res = std::max(1, per_cu * cus);
   }
-  // rows owned by workgroups: about 8 rows each, at most kRowsOwnedMax
-  const int nb_owned = std::max(1, std::min({(j.total_rows + 7) / 8, resident[dev][1], max_blocks, kTargetBlocksMax}));
-  if (j.window <= 64 && j.D <= 128 && (j.total_rows + nb_owned - 1) / nb_owned <= kRowsOwnedMax) {
-    hipLaunchKernelGGL(joint_owned, dim3(nb_owned), dim3(256), 0, s, j, rs);
-    return hipGetLastError();
-  }
-  const int nb = std::max(1, std::min({j.window * n_rb, resident[dev][0], max_blocks}));
-  hipLaunchKernelGGL(joint_persistent, dim3(nb), dim3(256), 0, s, j, rs);
+  // about one row per wave, at most one workgroup per compute unit
+  const int nb = std::max(1, std::min({(j.total_rows + kJW - 1) / kJW, res, kJointBlocksMax}));
+  if (lds && (j.total_rows + nb - 1) / nb > kRowsOwnedMax) return hipErrorInvalidConfiguration;
+  hipLaunchKernelGGL(kern, dim3(nb), dim3(kJT), 0, s, j);
   return hipGetLastError();
 }
 

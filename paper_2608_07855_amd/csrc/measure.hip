@@ -600,8 +600,13 @@ __global__ __launch_bounds__(kNW * 64, 1) void page_kernel(AttnGeom a, PageWork 
   if (MODE == 1) n_items = min(*pw.n_cand, pw.n_items);
   if (MODE == 1 && pw.clear && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && tid < pw.n_clear)
     pw.clear[tid] = 0;
-  const int i_begin = blockIdx.x * pw.items_per_block;
-  const int i_end = min(n_items, i_begin + pw.items_per_block);
+  // MODE 0: a run of pages.  MODE 1: every gridDim.x-th candidate, since the
+  // host knows only a bound of their number (34 candidates under a bound of
+  // 256 on 256 workgroups: 46 us with runs of 8, which left 5 of 32 blocks
+  // with work, 23 us spread)
+  const int i_begin = MODE == 0 ? (int)blockIdx.x * pw.items_per_block : 0;
+  const int i_end = MODE == 0 ? min(n_items, i_begin + pw.items_per_block)
+                              : (n_items - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
   if (i_begin >= i_end) return;
   const uint16_t* kh = a.k + (int64_t)g * a.kv_head_stride;
   const uint16_t* vh = a.v + (int64_t)g * a.kv_head_stride;
@@ -610,8 +615,7 @@ __global__ __launch_bounds__(kNW * 64, 1) void page_kernel(AttnGeom a, PageWork 
   // on a global load inside the loop (a wait there would also drain the
   // loads issued ahead); an invalid candidate index is an empty page
   for (int i = tid; i < i_end - i_begin; i += NT) {
-    const int item = i_begin + i;
-    const int pg = MODE == 0 ? item : pw.cand[item];
+    const int pg = MODE == 0 ? i_begin + i : pw.cand[blockIdx.x + i * gridDim.x];
     const bool ok = pg >= 0 && pg < pw.n_pages;
     sItStart[i] = ok ? pw.start[pg] : 0;
     // the length, and above bit 8 (MODE 0) where the page meets the window
@@ -701,6 +705,7 @@ __global__ __launch_bounds__(kNW * 64, 1) void page_kernel(AttnGeom a, PageWork 
   // page `item` of the tile in buffer b, at slot ps (a constant at each call,
   // so the slot's LDS offsets fold into the instructions)
   auto page = [&](int b, int item, int m, const int ps) {
+    const int t_cand = blockIdx.x + item * gridDim.x;   // MODE 1: the candidate
     {
       const int lw = sItLen[item - i_begin];
       const int len = lw & 0xff, cross = lw >> 8;
@@ -777,7 +782,7 @@ __global__ __launch_bounds__(kNW * 64, 1) void page_kernel(AttnGeom a, PageWork 
 #pragma unroll
           for (int r = 0; r < 16; ++r) n2 = __builtin_fmaf(u[j][r], u[j][r], n2);
         if (MODE == 1 && ri.ok) {
-          float* rrow = pw.resid + (size_t)CKV_IDX((size_t)ri.rg * pw.n_items + item,
+          float* rrow = pw.resid + (size_t)CKV_IDX((size_t)ri.rg * pw.n_items + t_cand,
                                                    (int64_t)pw.total_rows * pw.n_items, a.dbg, 6) * D;
 #pragma unroll
           for (int j = 0; j < 2; ++j)
@@ -845,7 +850,7 @@ __global__ __launch_bounds__(kNW * 64, 1) void page_kernel(AttnGeom a, PageWork 
           atomicMax(rm, __float_as_uint(ratio));
         }
       } else if (ri.ok) {
-        const size_t base_i = (size_t)ri.rg * pw.n_items + item;
+        const size_t base_i = (size_t)ri.rg * pw.n_items + t_cand;
         if (half == 0) {
           pw.resA[base_i] = A;
           pw.resC[base_i] = c;
