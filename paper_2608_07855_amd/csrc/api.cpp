@@ -1054,8 +1054,9 @@ extern "C" int ckv_joint_test(ckv_ctx* c, const ckv_kv_view* kv, const ckv_windo
     plan.add(&j.st_nv, total_rows);
     plan.add(&j.st_fix, 2 * (size_t)total_rows);
   }
-  plan.add(&j.ctrl, 8);
+  plan.add(&j.ctrl, ckv::kJointCtrlWords);
   plan.add(&j.bmax, ckv::kJointBmaxWords);
+  plan.add(&j.gmax, ckv::kJointGmaxWords);
   if (!union_R) plan.add(&j.ur, max_cand);
   plan.add(&j.acc_t, std::max(pages->n_pages, 1));
   j.fix_cap = 2 * ckv::kJointWindow * total_rows;
@@ -1090,7 +1091,7 @@ extern "C" int ckv_joint_test(ckv_ctx* c, const ckv_kv_view* kv, const ckv_windo
     pw.total_rows = total_rows;
     pw.lse_scale = kLog2eHost;
     pw.clear = j.ctrl;
-    pw.n_clear = 8;
+    pw.n_clear = ckv::kJointCtrlWords;
     CKV_LAUNCH(c, "joint_residual", launch_page_kernel(a, pw, rs, 1, max_page_len(pages), c->stream));
   }
   // with no pages the joint kernel only writes the outputs

@@ -223,8 +223,9 @@ struct JointArgs {
   float* st_on;
   int* st_nv;
   unsigned long long* st_fix;
-  int* ctrl;              // [8] control words (zero before the launch: the residual pass clears them)
+  int* ctrl;              // [kJointCtrlWords] control words (zero before the launch: the residual pass clears them)
   unsigned int* bmax;     // [256 workgroups][2 guesses][window] maxima of a round
+  unsigned int* gmax;     // [16 groups][2 guesses][window]
   float tau;
   long long barrier_ticks; // bound of a grid-wide wait (100 MHz wall clock ticks)
   uint32_t* nonfinite;    // latched when an o or lse row is NaN or infinite (or null)
@@ -248,6 +249,8 @@ struct JointArgs {
 };
 constexpr int kJointWindow = 32;        // candidates tested per round
 constexpr int kJointBmaxWords = 256 * 2 * kJointWindow;
+constexpr int kJointGmaxWords = 16 * 2 * kJointWindow;
+constexpr int kJointCtrlWords = 20 * 32;
 constexpr float kJointFixA = 0.8f;      // union mass above which a pair is recomputed
 constexpr int kJointFixItems = 30720;   // (pair, segment) items of the fix-up workspace
 int joint_vis_slices(int S);

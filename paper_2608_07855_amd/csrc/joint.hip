@@ -27,9 +27,9 @@
 // itself, in LDS (or its own part of global memory when a workgroup owns
 // more than kRowsOwnedMax rows), so a round reads only the candidates'
 // residual rows and publishes one maximum per candidate and guess.  The
-// workgroup that arrives last reduces the maxima, decides and publishes the
-// decision in one 64-bit word that the others poll: one grid-wide wait per
-// round.  Everything that crosses workgroups moves through agent-scope
+// workgroups that arrive last reduce the maxima, the very last one decides
+// and publishes the decision in one 64-bit word that the others poll: one
+// grid-wide wait per round.  Everything that crosses workgroups moves through agent-scope
 // atomics, so no fence (which would write back and invalidate the XCD's
 // whole L2) is needed.  The candidate count is read on the device, so the
 // call needs no host round trip; each round decides at least one candidate,
@@ -58,9 +58,14 @@
 
 namespace ckv {
 
-// control words (cleared by the residual pass before this kernel starts):
-// arrivals, error, listed pairs, and the 64-bit decision word (round << 32 | payload)
-enum { kArrive = 0, kError = 1, kFixN = 2, kWord = 4 };
+// Control words (cleared by the residual pass before this kernel starts),
+// each on a 128-byte line of its own: pollers of the decision word and the
+// arrival counts do not meet.  Arrivals are counted in groups of kJointGroup
+// workgroups, then over the groups.
+constexpr int kLine = 32;   // ints
+enum { kWord = 0, kError = kLine, kFixN = 2 * kLine, kTop = 3 * kLine, kGroup0 = 4 * kLine };
+constexpr int kJointGroup = 16;
+static_assert(kGroup0 + 16 * kLine == kJointCtrlWords, "control words");
 // payload of a decision: mode (1: chain) | n << 1 | extra << 7 | flags
 constexpr unsigned kDecChain = 1u, kDecExtra = 1u << 7, kDecResolve = 1u << 8, kDecDefer = 1u << 9,
                    kDecFlush = 1u << 10;
@@ -79,50 +84,6 @@ __device__ __forceinline__ T ld_agent(const T* p) {
 template <class T>
 __device__ __forceinline__ void st_agent(T* p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Arrival of this workgroup; true in the workgroup that completes `target`
-// arrivals.  Every wave first waits for its own stores.
-__device__ bool joint_arrive(int* ctrl, int target, int* s_flag) {
-  wait_own_stores();
-  __syncthreads();
-  if (threadIdx.x == 0)
-    *s_flag = __hip_atomic_fetch_add(&ctrl[kArrive], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == target - 1;
-  __syncthreads();
-  return *s_flag != 0;
-}
-
-// Thread 0 polls `ready` until it holds, the bound runs out or another
-// workgroup gave up; false (in every thread) in the last two cases.
-template <class F>
-__device__ bool joint_wait(int* ctrl, long long timeout, int* s_flag, F ready) {
-  if (threadIdx.x == 0) {
-    const long long t0 = wall_clock64();
-    int ok = 1;
-    if (timeout <= 0) {   // a zero bound gives up at once: the failure path, forced
-      st_agent(&ctrl[kError], 1);
-      ok = 0;
-    }
-    while (ok && !ready()) {
-      if (ld_agent(&ctrl[kError]) != 0 || wall_clock64() - t0 >= timeout) {
-        st_agent(&ctrl[kError], 1);
-        ok = 0;
-        break;
-      }
-      __builtin_amdgcn_s_sleep(1);
-    }
-    *s_flag = ok;
-  }
-  __syncthreads();
-  const bool ok = *s_flag != 0;
-  __syncthreads();
-  return ok;
-}
-
-__device__ bool joint_barrier(int* ctrl, int target, long long timeout, int* s_flag) {
-  joint_arrive(ctrl, target, s_flag);
-  __syncthreads();
-  return joint_wait(ctrl, timeout, s_flag, [&] { return ld_agent(&ctrl[kArrive]) >= target; });
 }
 
 __device__ __forceinline__ void store_pair(int* p, int2 v) {
@@ -292,41 +253,31 @@ __device__ void joint_tests(const JointArgs& j, const RowState& st, int rb0, int
   }
 }
 
-// The last workgroup of a round: maxima over the workgroups' words (bit 31:
-// some row of the workgroup left the pair to the fix-up), then the decision.
-// Two candidates' words per thread and load, every load issued at once.
-__device__ void joint_decide(const JointArgs& j, int cursor, int n_eff, int round, unsigned* sRed, int* sRedAny) {
-  constexpr int kGrp = kJT / 32, kPer = kJointBlocksMax / kGrp;
-  const int tid = threadIdx.x;
+// Maxima over n <= 16 rows of 64 words (one per candidate and guess; bit 31:
+// some row left the pair to the fix-up) into LDS: every load of the block at once.
+__device__ void joint_reduce(const unsigned* words, int n, unsigned* sRed, int* sRedAny) {
+  const int tid = threadIdx.x, w = tid & 31, b = tid >> 5;
+  static_assert(kJT / 32 == kJointGroup, "one word pair per thread");
   if (tid < 64) {
     sRed[tid] = 0u;
     sRedAny[tid] = 0;
   }
+  const unsigned long long v = b < n ? ld_agent(reinterpret_cast<const unsigned long long*>(words) + b * 32 + w) : 0ull;
   __syncthreads();
-  {
-    const int w = tid & 31, grp = tid >> 5;
-    const unsigned long long* src = reinterpret_cast<const unsigned long long*>(j.bmax);
-    unsigned long long v[kPer];
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-      const int b = grp + kGrp * q;
-      v[q] = b < (int)gridDim.x ? ld_agent(&src[(size_t)b * 32 + w]) : 0ull;
-    }
-    unsigned m0 = 0u, m1 = 0u, any = 0u;
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-      const unsigned lo = (unsigned)v[q], hi = (unsigned)(v[q] >> 32);
-      m0 = max(m0, lo & 0x7fffffffu);
-      m1 = max(m1, hi & 0x7fffffffu);
-      any |= (lo >> 31) | ((hi >> 31) << 1);
-    }
-    if (m0) atomicMax(&sRed[2 * w], m0);
-    if (m1) atomicMax(&sRed[2 * w + 1], m1);
-    if (any & 1u) sRedAny[2 * w] = 1;
-    if (any & 2u) sRedAny[2 * w + 1] = 1;
-  }
+  const unsigned lo = (unsigned)v, hi = (unsigned)(v >> 32);
+  if (lo & 0x7fffffffu) atomicMax(&sRed[2 * w], lo & 0x7fffffffu);
+  if (hi & 0x7fffffffu) atomicMax(&sRed[2 * w + 1], hi & 0x7fffffffu);
+  if (lo >> 31) sRedAny[2 * w] = 1;
+  if (hi >> 31) sRedAny[2 * w + 1] = 1;
   __syncthreads();
-  if (tid >= 64) return;
+}
+
+// The decision of a round from its maxima (the workgroup that arrives last);
+// the payload in thread 0.
+__device__ unsigned joint_decide(const JointArgs& j, int cursor, int n_eff, const unsigned* sRed,
+                                 const int* sRedAny) {
+  const int tid = threadIdx.x;
+  if (tid >= 64) return 0u;
   const int c = tid & 31, t = cursor + c;
   const float r = __uint_as_float(sRed[tid]);
   const bool any = sRedAny[tid] != 0, valid = t < n_eff;
@@ -351,13 +302,77 @@ __device__ void joint_decide(const JointArgs& j, int cursor, int n_eff, int roun
     const int ap = j.cand[t];
     if (ap >= 0 && ap < j.n_pages) st_agent(&j.acc_t[ap], t);
   }
-  if (tid == 0) {
-    unsigned p = (chain ? kDecChain : 0u) | (unsigned)n << 1 | (extra ? kDecExtra : 0u) |
-                 (resolve ? kDecResolve : 0u) | (defer ? kDecDefer : 0u);
-    // empty the list first unless it has room for a whole round's pairs
-    if ((defer || resolve) && ld_agent(&j.ctrl[kFixN]) > kJointWindow * j.total_rows) p |= kDecFlush;
-    st_agent(reinterpret_cast<unsigned long long*>(j.ctrl + kWord), (unsigned long long)round << 32 | p);
+  unsigned p = (chain ? kDecChain : 0u) | (unsigned)n << 1 | (extra ? kDecExtra : 0u) |
+               (resolve ? kDecResolve : 0u) | (defer ? kDecDefer : 0u);
+  // empty the list first unless it has room for a whole round's pairs
+  if ((defer || resolve) && ld_agent(&j.ctrl[kFixN]) > kJointWindow * j.total_rows) p |= kDecFlush;
+  return p;
+}
+
+struct JointSync {
+  unsigned* sRed;
+  int* sRedAny;
+  int* s_flag;
+  unsigned long long* s_word;
+  int epoch;    // grid-wide waits so far
+};
+
+// Grid-wide wait.  With `tests`, the workgroups' maxima (j.bmax) are reduced
+// on the way -- by the last workgroup of each group over its group, then by
+// the last group over the groups -- and that workgroup's decision travels
+// back in the word the others poll: one round trip per round (about 6 us;
+// two barriers of 256 arrivals at one counter with a reduction of all
+// workgroups' words between them took 17).  Every wave waits for its own
+// stores before its workgroup arrives.  False (in every thread) if the bound
+// ran out here or elsewhere.
+__device__ bool joint_sync(const JointArgs& j, JointSync& sy, bool tests, int cursor, int n_eff, unsigned* payload) {
+  const int tid = threadIdx.x;
+  const int grp = blockIdx.x / kJointGroup, n_grp = (gridDim.x + kJointGroup - 1) / kJointGroup;
+  const int gs = min(kJointGroup, (int)gridDim.x - grp * kJointGroup);
+  unsigned long long* word = reinterpret_cast<unsigned long long*>(j.ctrl + kWord);
+  ++sy.epoch;
+  auto arrive = [&](int* count, int target) {
+    wait_own_stores();
+    __syncthreads();
+    if (tid == 0)
+      *sy.s_flag = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == target - 1;
+    __syncthreads();
+    return *sy.s_flag != 0;
+  };
+  if (arrive(&j.ctrl[kGroup0 + kLine * grp], sy.epoch * gs)) {
+    if (tests) {
+      joint_reduce(j.bmax + (size_t)grp * kJointGroup * 64, gs, sy.sRed, sy.sRedAny);
+      if (tid < 64) st_agent(&j.gmax[grp * 64 + tid], sy.sRed[tid] | (sy.sRedAny[tid] ? 0x80000000u : 0u));
+    }
+    if (arrive(&j.ctrl[kTop], sy.epoch * n_grp)) {
+      unsigned p = 0u;
+      if (tests) {
+        joint_reduce(j.gmax, n_grp, sy.sRed, sy.sRedAny);
+        p = joint_decide(j, cursor, n_eff, sy.sRed, sy.sRedAny);
+      }
+      if (tid == 0) st_agent(word, (unsigned long long)sy.epoch << 32 | p);
+    }
   }
+  __syncthreads();
+  if (tid == 0) {
+    const long long t0 = wall_clock64();
+    unsigned long long w = 0;
+    int ok = j.barrier_ticks > 0;   // a zero bound gives up at once: the failure path, forced
+    while (ok) {
+      w = ld_agent(word);
+      if ((w >> 32) == (unsigned long long)sy.epoch) break;
+      if (ld_agent(&j.ctrl[kError]) != 0 || wall_clock64() - t0 >= j.barrier_ticks) ok = 0;
+      __builtin_amdgcn_s_sleep(1);
+    }
+    if (!ok) st_agent(&j.ctrl[kError], 1);
+    *sy.s_word = w;
+    *sy.s_flag = ok;
+  }
+  __syncthreads();
+  const bool ok = *sy.s_flag != 0;
+  if (payload) *payload = (unsigned)*sy.s_word;
+  __syncthreads();
+  return ok;
 }
 
 // Lists the fix-up pairs of the candidates in the masks (bits as in
@@ -533,9 +548,8 @@ __device__ void joint_fix_final(const JointArgs& j, int e0, int np, int parts, f
 // Recomputes every listed pair and empties the list (in every workgroup; the
 // first barrier publishes the workgroups' appends).
 template <int D>
-__device__ bool joint_flush(const JointArgs& j, int& target, int* s_flag, float* sacc, uint8_t* sMask) {
-  target += gridDim.x;
-  if (!joint_barrier(j.ctrl, target, j.barrier_ticks, s_flag)) return false;
+__device__ bool joint_flush(const JointArgs& j, JointSync& sy, float* sacc, uint8_t* sMask) {
+  if (!joint_sync(j, sy, false, 0, 0, nullptr)) return false;
   const int n = min(ld_agent(&j.ctrl[kFixN]), j.fix_cap);
   if (n == 0) return true;   // the same in every block
   const int S = j.geo.S;
@@ -547,12 +561,10 @@ __device__ bool joint_flush(const JointArgs& j, int& target, int* s_flag, float*
     const int np = min(npc, n - e0);
     if (j.geo.slot) joint_fix_partial<D, true>(j, e0, np, seg, parts, sacc, sMask);
     else joint_fix_partial<D, false>(j, e0, np, seg, parts, sacc, sMask);
-    target += gridDim.x;
-    if (!joint_barrier(j.ctrl, target, j.barrier_ticks, s_flag)) return false;
+    if (!joint_sync(j, sy, false, 0, 0, nullptr)) return false;
     if (e0 + npc >= n && blockIdx.x == 0 && threadIdx.x == 0) st_agent(&j.ctrl[kFixN], 0);   // read by all above
     joint_fix_final<D>(j, e0, np, parts, sacc);
-    target += gridDim.x;
-    if (!joint_barrier(j.ctrl, target, j.barrier_ticks, s_flag)) return false;
+    if (!joint_sync(j, sy, false, 0, 0, nullptr)) return false;
   }
   return true;
 }
@@ -625,11 +637,11 @@ __global__ __launch_bounds__(kJT) void joint_rounds(JointArgs j) {
     st.C[r] = 0;
     if (lane == 0 && (!(n2 <= 3.4e38f) || !(j.lse[row] < INFINITY))) latch_nonfinite(j.nonfinite);
   }
-  int target = gridDim.x;
+  JointSync sy{sRed, sRedAny, &s_flag, &s_word, 0};
   auto give_up = [&] {
     if (tid == 0) st_agent(j.n_accepted, -1);
   };
-  if (!joint_barrier(j.ctrl, target, j.barrier_ticks, &s_flag)) return give_up();
+  if (!joint_sync(j, sy, false, 0, 0, nullptr)) return give_up();
   for (int r = wave; r < nr; r += kJW) {
     const int row = rb0 + r;
     int c = 0;
@@ -641,7 +653,7 @@ __global__ __launch_bounds__(kJT) void joint_rounds(JointArgs j) {
   int cursor = 0, n_acc = 0, f0 = 0, nf = 0;
   bool listed = false;
   // every round decides at least one candidate: n_eff rounds suffice
-  for (int round = 1; cursor < n_eff; ++round) {
+  while (cursor < n_eff) {
     if (tid < 64) {
       sMax[tid] = 0u;
       sAny[tid] = 0;
@@ -651,21 +663,13 @@ __global__ __launch_bounds__(kJT) void joint_rounds(JointArgs j) {
     __syncthreads();
     // this workgroup's maxima go to its own words (no contended atomics)
     if (tid < 64) st_agent(&j.bmax[(size_t)blockIdx.x * 64 + tid], sMax[tid] | (sAny[tid] ? 0x80000000u : 0u));
-    target += gridDim.x;
-    if (joint_arrive(j.ctrl, target, &s_flag)) joint_decide(j, cursor, n_eff, round, sRed, sRedAny);
-    __syncthreads();
-    const unsigned long long* word = reinterpret_cast<const unsigned long long*>(j.ctrl + kWord);
-    if (!joint_wait(j.ctrl, j.barrier_ticks, &s_flag, [&] {
-          s_word = ld_agent(word);
-          return (s_word >> 32) == (unsigned long long)round;
-        }))
-      return give_up();
-    const unsigned dec = (unsigned)s_word;
+    unsigned dec;
+    if (!joint_sync(j, sy, true, cursor, n_eff, &dec)) return give_up();
     const bool chain = dec & kDecChain;
     const int n = (dec >> 1) & 63, extra = (dec & kDecExtra) ? 1 : 0;
     f0 = chain ? cursor : cursor + n;    // the candidates accepted in this round
     nf = chain ? n : extra;
-    if ((dec & kDecFlush) && !joint_flush<D>(j, target, &s_flag, sacc, sMask)) return give_up();
+    if ((dec & kDecFlush) && !joint_flush<D>(j, sy, sacc, sMask)) return give_up();
     if (dec & (kDecDefer | kDecResolve)) {
       // candidates [0, nd) of the chosen guess, as bits of RowState::fix
       const int nd = (dec & kDecResolve) ? 1 : n + extra;
@@ -678,7 +682,7 @@ __global__ __launch_bounds__(kJT) void joint_rounds(JointArgs j) {
     }
     if (dec & kDecResolve) {
       // the candidate at the cursor: its union effect is complete after a flush
-      if (!joint_flush<D>(j, target, &s_flag, sacc, sMask)) return give_up();
+      if (!joint_flush<D>(j, sy, sacc, sMask)) return give_up();
       listed = false;
       const bool pass = ld_agent(&j.ur[cursor]) <= j.tau;
       f0 = cursor;
@@ -694,7 +698,7 @@ __global__ __launch_bounds__(kJT) void joint_rounds(JointArgs j) {
     }
     n_acc += nf;
   }
-  if (listed && !joint_flush<D>(j, target, &s_flag, sacc, sMask)) return give_up();
+  if (listed && !joint_flush<D>(j, sy, sacc, sMask)) return give_up();
   if (gid == 0 && ld_agent(&j.ctrl[kError]) == 0) st_agent(j.n_accepted, n_acc);
 }
 

@@ -598,8 +598,8 @@ __global__ __launch_bounds__(kNW * 64, 1) void page_kernel(AttnGeom a, PageWork 
   const int half = lane >> 5, col = lane & 31;
   int n_items = pw.n_items;
   if (MODE == 1) n_items = min(*pw.n_cand, pw.n_items);
-  if (MODE == 1 && pw.clear && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && tid < pw.n_clear)
-    pw.clear[tid] = 0;
+  if (MODE == 1 && pw.clear && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)
+    for (int i = tid; i < pw.n_clear; i += NT) pw.clear[i] = 0;
   // MODE 0: a run of pages.  MODE 1: every gridDim.x-th candidate, since the
   // host knows only a bound of their number (34 candidates under a bound of
   // 256 on 256 workgroups: 46 us with runs of 8, which left 5 of 32 blocks
