@@ -463,9 +463,11 @@ int mass_chunk(const AttnGeom& a) {
   return (int)round_up(ceil_div(a.S, std::max(1, kMassBlocks / a.Hkv)), 64);
 }
 
-int items_per_block(int n_items, int other_blocks) {
-  const int per = ceil_div(n_items * std::max(other_blocks, 1), kTargetBlocks);
-  return std::min(ckv::kPageItemsMax, std::max(1, per));
+// pages (or candidates) per page-kernel workgroup of nw waves: `target`
+// workgroups over the row blocks and KV heads of the call
+int items_per_block(const AttnGeom& a, int n_items, int nw, int target) {
+  const int64_t total = (int64_t)n_items * a.Hkv * ceil_div(a.rows, 32 * nw);
+  return std::min(page_items_limit(nw, a.W, a.group), std::max(1, (int)((total + target - 1) / target)));
 }
 
 }  // namespace
@@ -670,11 +672,9 @@ struct MeasureBufs {
 
 void plan_measure(const AttnGeom& a, int n_splits, float* o, Plan& plan, MeasureBufs& b) {
   const int D = a.D, total_rows = a.Hq * a.W;
-  const int rpb = rows_per_block_attention();
-  const int nrb = ceil_div(a.rows, rpb);
   const int chunk = (int)round_up(ceil_div(a.S, n_splits), 64);
   n_splits = ceil_div(a.S, chunk);
-  b.sp = AttnSplit{chunk, n_splits, nrb * rpb, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+  b.sp = AttnSplit{chunk, n_splits, a.rows, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   b.rs = RowStats{o, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   const size_t nsr = (size_t)a.Hkv * n_splits * b.sp.rows_pad;
   plan.add(&b.sp.part_o, nsr * D);
@@ -699,7 +699,7 @@ void plan_measure(const AttnGeom& a, int n_splits, float* o, Plan& plan, Measure
 // splits of the window pass: about one workgroup per compute unit, and at
 // most kMaxSplitTokens tokens per split
 int default_splits(const AttnGeom& a) {
-  const int nrb = ceil_div(a.rows, rows_per_block_attention());
+  const int nrb = ceil_div(a.rows, 32 * max_waves());
   return std::max(1, std::min(ceil_div(a.S, 64),
                               std::max(ceil_div(kTargetBlocks, a.Hkv * nrb), ceil_div(a.S, kMaxSplitTokens))));
 }
@@ -716,35 +716,55 @@ int check_measure(ckv_ctx* c, const ckv_kv_view* kv, const ckv_window_view* win,
   return CKV_OK;
 }
 
+// what the kernels of one problem read (page_blocks: page workgroups of nw
+// waves aimed at)
+MeasureProb make_prob(const ckv_ctx* c, const AttnGeom& a, const MeasureBufs& b, const int32_t* dstart,
+                      const int32_t* dlen, int n, int nw, int page_blocks, float* R, float* R_head, float* lse,
+                      float* token_mass) {
+  const int total_rows = a.Hq * a.W;
+  MeasureProb p;
+  std::memset(static_cast<void*>(&p), 0, sizeof p);
+  p.a = a;
+  p.sp = b.sp;
+  p.rs = b.rs;
+  p.zl = ZeroList{R, R ? (size_t)n : 0, R_head, R_head ? (size_t)n * a.Hq : 0, token_mass,
+                  token_mass ? (size_t)a.S : 0, b.fix_count, b.arrive, (size_t)total_rows, c->nf_dev};
+  p.lse_out = lse;
+  p.fpart = b.fpart;
+  p.arrive = b.arrive;
+  p.mass = token_mass;
+  p.mass_chunk = mass_chunk(a);
+  PageWork& pw = p.pw;
+  pw.start = dstart;
+  pw.len = dlen;
+  pw.n_items = n;
+  pw.n_pages = n;
+  pw.items_per_block = items_per_block(a, n, nw, page_blocks);
+  pw.R = R;
+  pw.R_head = R_head;
+  pw.lse_scale = 1.f;
+  pw.Hq = a.Hq;
+  pw.total_rows = total_rows;
+  pw.fix_list = b.fix_list;
+  pw.fix_count = b.fix_count;
+  pw.fix_cap = total_rows;
+  pw.fix_a = ckv::kFixA;
+  pw.fix_a_hi = ckv::kFixAHi;
+  pw.split_tokens = b.sp.chunk;
+  return p;
+}
+
 // the kernels of one measurement call, enqueued on the context's stream
 int enqueue_measure(ckv_ctx* c, const AttnGeom& a, const MeasureBufs& b, const int32_t* dstart,
                     const int32_t* dlen, const ckv_page_list* pages, float* R, float* R_head, float* lse,
                     float* token_mass) {
-  const int n = pages->n_pages, total_rows = a.Hq * a.W;
+  const int n = pages->n_pages, max_len = max_page_len(pages);
+  const MeasureProb p = make_prob(c, a, b, dstart, dlen, n, max_waves(), kTargetBlocks, R, R_head, lse, token_mass);
   CKV_LAUNCH(c, "window_attention", launch_window_attention(a, b.sp, c->stream));
-  ZeroList zl{R, R ? (size_t)n : 0, R_head, R_head ? (size_t)n * a.Hq : 0, token_mass,
-              token_mass ? (size_t)a.S : 0, b.fix_count, b.arrive, (size_t)total_rows, c->nf_dev};
-  CKV_LAUNCH(c, "combine", launch_combine(a, b.sp, b.rs, lse, zl, c->stream));
+  CKV_LAUNCH(c, "combine", launch_combine(a, b.sp, b.rs, lse, p.zl, c->stream));
   if (n > 0) {
-    PageWork pw{};
-    pw.start = dstart;
-    pw.len = dlen;
-    pw.n_items = n;
-    pw.n_pages = n;
-    pw.items_per_block = std::min(items_per_block(n, a.Hkv * ceil_div(a.rows, rows_per_block_page())),
-                                  ckv::kPageRmaxCap / page_heads_per_block(a.W, a.group));
-    pw.R = R;
-    pw.R_head = R_head;
-    pw.lse_scale = 1.f;
-    pw.Hq = a.Hq;
-    pw.total_rows = total_rows;
-    pw.fix_list = b.fix_list;
-    pw.fix_count = b.fix_count;
-    pw.fix_cap = total_rows;
-    pw.fix_a = ckv::kFixA;
-    pw.fix_a_hi = ckv::kFixAHi;
-    pw.split_tokens = b.sp.chunk;
-    CKV_LAUNCH(c, "page_effect", launch_page_kernel(a, pw, b.rs, 0, max_page_len(pages), c->stream));
+    const PageWork& pw = p.pw;
+    CKV_LAUNCH(c, "page_effect", launch_page_kernel(a, pw, b.rs, 0, max_len, c->stream));
     if (token_mass && mass_fixup_applies(a)) {
       // the fix-up runs in the shadow of the token mass, in one launch
       CKV_LAUNCH(c, "token_mass_fixup", launch_mass_fixup(a, b.sp, b.rs, pw, b.fpart, b.arrive, ckv::kFixParts,
@@ -754,6 +774,107 @@ int enqueue_measure(ckv_ctx* c, const AttnGeom& a, const MeasureBufs& b, const i
     CKV_LAUNCH(c, "page_fixup", launch_page_fixup(a, b.sp, b.rs, pw, b.fpart, b.arrive, ckv::kFixParts, 0, c->stream));
   }
   if (token_mass) CKV_LAUNCH(c, "token_mass", launch_token_mass(a, b.rs, token_mass, mass_chunk(a), c->stream));
+  return CKV_OK;
+}
+
+// One problem of a batch as the caller gave it.
+struct BatchItem {
+  AttnGeom a;
+  const ckv_page_list* pages;
+  int max_len;
+  float *R, *R_head, *o, *lse, *mass;
+};
+
+bool same_kernels(const BatchItem& x, const BatchItem& y) {
+  if (x.a.D != y.a.D || !x.a.slot != !y.a.slot || batch_waves(x.a.rows) != batch_waves(y.a.rows) ||
+      page_row_groups(batch_waves(x.a.rows), x.a.rows) != page_row_groups(batch_waves(y.a.rows), y.a.rows) ||
+      (x.max_len > 32) != (y.max_len > 32) || !x.mass != !y.mass)
+    return false;
+  if (!x.mass) return true;
+  const int ppw = mass_pairs_per_wave(x.a);
+  return ppw == mass_pairs_per_wave(y.a) && (ppw == 0 || mass_slices(x.a, ppw) == mass_slices(y.a, ppw));
+}
+
+// Working memory of the problems one launch serves together, at most.  At
+// 4224 tokens and 40 window rows per KV head (7 MB a problem) that is the
+// whole of a 40-layer commit; a 65536-token layer (45 MB) fills the device by
+// itself, and 8 share a launch.
+constexpr size_t kBatchBytes = size_t(384) << 20;
+constexpr int kBatchMax = 4096;   // problems of one launch (grid z)
+
+// Workspace of one problem of a batch (its page table is copied there too).
+void plan_item(const BatchItem& it, Plan& plan, MeasureBufs& b, int32_t*& table) {
+  plan_measure(it.a, default_splits(it.a), it.o, plan, b);
+  plan.add(&table, 2 * (size_t)std::max(it.pages->n_pages, 1));
+}
+
+// Enqueues problems it[0 .. n), which agree in their kernels, as one launch
+// per kernel.  CKV_ERR_NOMEM (nothing enqueued) if their workspace cannot be had.
+int enqueue_batch(ckv_ctx* c, const BatchItem* it, int n) {
+  Plan plan;
+  std::vector<MeasureBufs> bufs(n);
+  std::vector<int32_t*> table(n, nullptr);
+  MeasureProb* dev = nullptr;
+  // the arguments and the page tables first, so that one copy brings them
+  plan.add(&dev, n);
+  size_t head = plan.total;
+  for (int i = 0; i < n; ++i) {
+    plan.add(&table[i], 2 * (size_t)std::max(it[i].pages->n_pages, 1));
+  }
+  const size_t copy_bytes = plan.total;
+  for (int i = 0; i < n; ++i) plan_measure(it[i].a, default_splits(it[i].a), it[i].o, plan, bufs[i]);
+  int rc = realize(c, plan);
+  if (rc) return rc;
+  MeasureBatch b{};
+  b.n = n;
+  b.D = it[0].a.D;
+  b.nw = batch_waves(it[0].a.rows);
+  b.paged = it[0].a.slot != nullptr;
+  b.page_groups = page_row_groups(b.nw, it[0].a.rows);
+  b.two = it[0].max_len > 32;
+  b.mass_ppw = it[0].mass ? mass_pairs_per_wave(it[0].a) : 0;
+  b.mass_nz = b.mass_ppw ? mass_slices(it[0].a, b.mass_ppw) : 1;
+  // (pair, part) items of a fix-up list are a chain of latencies each, so a
+  // problem's list gets a block per item where it is short
+  b.fix_blocks = std::max(32, 8 * kTargetBlocks / n);
+  // the workgroups of the window and page kernels that the device holds at
+  // once; each takes about a third of its even share of the batch's splits
+  // and half of its share of the pages, so the last ones to finish idle little
+  const int resident = kTargetBlocks * (b.nw == 4 ? 2 : 1);
+  int64_t units = 0;
+  for (int i = 0; i < n; ++i)
+    units += (int64_t)bufs[i].sp.n_splits * it[i].a.Hkv * ceil_div(it[i].a.rows, 32 * b.nw);
+  const int per = (int)std::max<int64_t>(1, units / (3 * resident));
+  std::vector<char> blob(copy_bytes, 0);
+  for (int i = 0; i < n; ++i) {
+    const BatchItem& x = it[i];
+    const int np = x.pages->n_pages;
+    MeasureProb p = make_prob(c, x.a, bufs[i], table[i], table[i] + np, np, b.nw, std::max(2 * resident / n, 1), x.R,
+                              x.R_head, x.lse, x.mass);
+    p.splits_per_block = std::min(per, p.sp.n_splits);
+    std::memcpy(blob.data() + i * sizeof(MeasureProb), &p, sizeof p);
+    if (np > 0) {
+      std::memcpy(blob.data() + head, x.pages->start, np * sizeof(int32_t));
+      std::memcpy(blob.data() + head + np * sizeof(int32_t), x.pages->len, np * sizeof(int32_t));
+    }
+    head += round_up(2 * (size_t)std::max(np, 1) * sizeof(int32_t), kAlign);
+    b.any_pages = b.any_pages || np > 0;
+    b.max_split_groups = std::max(b.max_split_groups, ceil_div(p.sp.n_splits, p.splits_per_block));
+    b.max_heads = std::max(b.max_heads, x.a.Hkv);
+    b.max_rb_heads = std::max(b.max_rb_heads, x.a.Hkv * ceil_div(x.a.rows, 32 * b.nw));
+    b.max_combine = std::max(b.max_combine, combine_blocks(x.a));
+    b.max_page_blocks = std::max(b.max_page_blocks, ceil_div(np, p.pw.items_per_block));
+    b.max_mass_x = std::max(b.max_mass_x, ceil_div(x.a.S, p.mass_chunk));
+  }
+  if ((rc = upload(c, blob.data(), blob.size(), dev))) return rc;
+  CKV_LAUNCH(c, "window_attention", launch_measure_batch(dev, b, 0, c->stream));
+  CKV_LAUNCH(c, "combine", launch_measure_batch(dev, b, 1, c->stream));
+  const bool fused = it[0].mass && b.mass_ppw > 0;
+  if (b.any_pages) {
+    CKV_LAUNCH(c, "page_effect", launch_measure_batch(dev, b, 2, c->stream));
+    if (!fused) CKV_LAUNCH(c, "page_fixup", launch_measure_batch(dev, b, 3, c->stream));
+  }
+  if (it[0].mass) CKV_LAUNCH(c, fused && b.any_pages ? "token_mass_fixup" : "token_mass", launch_measure_batch(dev, b, 4, c->stream));
   return CKV_OK;
 }
 
@@ -852,14 +973,47 @@ extern "C" int ckv_measure_page_effects_batch(ckv_ctx* c, int32_t n, const ckv_k
         (win[i].n_q_heads / kv[i].n_kv_heads) * win[i].n_rows > token_mass_max_rows())
       return fail(c, CKV_ERR_UNSUPPORTED, "batch problem %d: too many window rows for token_mass", i);
   }
-  for (int i = 0; i < n; ++i) {
-    const int rc = ckv_measure_page_effects(c, &kv[i], &win[i], &pages[i], R[i], R_head ? R_head[i] : nullptr,
-                                            o ? o[i] : nullptr, lse ? lse[i] : nullptr,
-                                            token_mass ? token_mass[i] : nullptr);
+  if (n == 0) return CKV_OK;
+  DeviceGuard g(c->device);
+  if (!g.ok) return fail(c, CKV_ERR_HIP, "cannot select device %d", c->device);
+  // runs of problems that share their kernels and whose workspace stays
+  // bounded go out together, the rest one by one
+  std::vector<BatchItem> items(n);
+  for (int i = 0; i < n; ++i)
+    items[i] = BatchItem{make_geom(c, &kv[i], &win[i]), &pages[i], max_page_len(&pages[i]), R[i],
+                         R_head ? R_head[i] : nullptr, o ? o[i] : nullptr, lse ? lse[i] : nullptr,
+                         token_mass ? token_mass[i] : nullptr};
+  auto one = [&](int i) -> int {
+    const BatchItem& x = items[i];
+    int rc = ckv_measure_page_effects(c, &kv[i], &win[i], x.pages, x.R, x.R_head, x.o, x.lse, x.mass);
     if (rc) {
       const std::string m = c->err;
       return fail(c, rc, "batch problem %d: %s", i, m.c_str());
     }
+    return CKV_OK;
+  };
+  const size_t cap = c->ws_limit ? std::min(c->ws_limit, kBatchBytes) : kBatchBytes;
+  for (int i = 0; i < n;) {
+    int m = 0;
+    for (size_t total = 0; i + m < n && m < kBatchMax && same_kernels(items[i], items[i + m]); ++m) {
+      Plan plan;
+      MeasureBufs b;
+      int32_t* table = nullptr;
+      plan_item(items[i + m], plan, b, table);
+      total += plan.total + round_up(sizeof(MeasureProb), kAlign);
+      if (m > 0 && total > cap) break;
+    }
+    int rc = m > 1 ? enqueue_batch(c, &items[i], m) : CKV_ERR_NOMEM;
+    if (rc == CKV_ERR_NOMEM) {
+      c->err.clear();
+      for (int k = 0; k < m; ++k)
+        if ((rc = one(i + k))) return rc;
+    }
+    if (rc) {
+      const std::string e = c->err;
+      return fail(c, rc, "batch problems %d..%d: %s", i, i + m - 1, e.c_str());
+    }
+    i += m;
   }
   return CKV_OK;
 }
@@ -920,8 +1074,7 @@ extern "C" int ckv_measure_recorded(ckv_ctx* c, const ckv_kv_view* kv, const ckv
     pw.len = dlen;
     pw.n_items = n;
     pw.n_pages = n;
-    pw.items_per_block = std::min(items_per_block(n, a.Hkv * ceil_div(a.rows, rows_per_block_page())),
-                                  ckv::kPageRmaxCap / page_heads_per_block(a.W, a.group));
+    pw.items_per_block = items_per_block(a, n, max_waves(), kTargetBlocks);
     pw.R = R;
     pw.R_head = R_head;
     pw.lse_scale = 1.f;
@@ -1080,8 +1233,7 @@ extern "C" int ckv_joint_test(ckv_ctx* c, const ckv_kv_view* kv, const ckv_windo
     pw.len = dlen;
     pw.n_items = max_cand;
     pw.n_pages = pages->n_pages;
-    pw.items_per_block = items_per_block(std::min(max_cand, pages->n_pages),
-                                         a.Hkv * ceil_div(a.rows, rows_per_block_page()));
+    pw.items_per_block = items_per_block(a, std::min(max_cand, pages->n_pages), max_waves(), kTargetBlocks);
     pw.cand = cand;
     pw.n_cand = n_cand;
     pw.Hq = a.Hq;

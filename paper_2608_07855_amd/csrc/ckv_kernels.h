@@ -30,7 +30,7 @@ struct AttnGeom {
 
 // split-sequence partials of pass A
 struct AttnSplit {
-  int chunk, n_splits, rows_pad;
+  int chunk, n_splits, rows_pad;   // rows_pad: rows per split in the arrays below
   float* part_o;   // [Hkv][n_splits][rows_pad][D]
   float* part_m;   // [Hkv][n_splits][rows_pad]  (log2 units)
   float* part_l;
@@ -59,8 +59,8 @@ struct RowStats {
 };
 
 // pages processed by pass B (MODE 0: item = page; MODE 1: item t = page cand[t])
-constexpr int kPageItemsMax = 256;   // pages (or candidates) per page-kernel workgroup
-constexpr int kPageRmaxCap = 4096;   // (page, head) maxima a MODE 0 workgroup keeps in LDS
+constexpr int kPageItemsMax = 256;   // pages (or candidates) per 8-wave page-kernel workgroup
+constexpr int kPageRmaxCap = 4096;   // (page, head) maxima such a MODE 0 workgroup keeps in LDS
 
 struct PageWork {
   const int32_t* start;
@@ -133,9 +133,10 @@ __device__ __forceinline__ void latch_nonfinite(uint32_t* flag) {
   if (flag) __hip_atomic_store(flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-int rows_per_block_attention();
-int rows_per_block_page();
-int page_heads_per_block(int W, int group);   // bound on the query heads of one workgroup
+int max_waves();              // waves (of 32 rows) of a window or page workgroup of a single call
+int batch_waves(int rows);    // the same of a batch, for `rows` window rows per KV head
+int page_row_groups(int nw, int rows);   // 2: each page of a tile has its own waves
+int page_items_limit(int nw, int W, int group);   // pages per page-kernel workgroup at most
 int token_mass_max_rows();
 
 hipError_t launch_window_attention(const AttnGeom& a, const AttnSplit& sp, hipStream_t s);
@@ -167,6 +168,38 @@ constexpr int kMassFixBlocks = 256;
 bool mass_fixup_applies(const AttnGeom& a);
 hipError_t launch_mass_fixup(const AttnGeom& a, const AttnSplit& sp, const RowStats& rs, const PageWork& pw,
                              float* fpart, int* arrive, int parts, float* mass, int chunk, hipStream_t s);
+
+// One problem of a batched measurement, as the kernels of the batch read it
+// from device memory, and the launch bounds of a batch.  Every problem of a
+// batch agrees in head width, paging, waves per block, page kind (any page
+// longer than 32 tokens) and token-mass form.
+struct MeasureProb {
+  AttnGeom a;
+  AttnSplit sp;
+  RowStats rs;
+  PageWork pw;            // n_pages 0: no pages
+  ZeroList zl;
+  float* lse_out;
+  float* fpart;
+  int* arrive;
+  float* mass;
+  int mass_chunk;
+  int splits_per_block;   // splits of the window pass that one workgroup takes
+};
+struct MeasureBatch {
+  int n, D, nw;
+  bool paged, two, any_pages;
+  int page_groups;        // row groups of the page workgroups (with nw = 4)
+  int max_split_groups, max_rb_heads, max_heads, max_combine, max_page_blocks;
+  int fix_blocks;         // fix-up blocks per problem
+  int mass_ppw;           // token mass: 1 or 2 (fast form), 0: general form
+  int mass_nz, max_mass_x;
+};
+int combine_blocks(const AttnGeom& a);
+int mass_pairs_per_wave(const AttnGeom& a);   // 1 or 2, or 0 when the general form serves the shape
+int mass_slices(const AttnGeom& a, int ppw);
+// kernel: 0 window, 1 combine, 2 page effects, 3 fix-up, 4 token mass (with the fix-up in its fast form)
+hipError_t launch_measure_batch(const MeasureProb* dev, const MeasureBatch& b, int kernel, hipStream_t s);
 
 // recorded window outputs: row statistics from the caller's o and natural-log
 // lse (nvis_part: workspace [W][recorded_slices(S)] ints, or null to skip the

@@ -18,10 +18,19 @@
 //   C. token_mass_kernel: max_h sum_p a_hpi for every token.
 // Logits are carried in log2 units: x = scale * log2(e) * q.k.
 //
-// Every kernel runs 8 waves of 32 window rows each (256 rows per workgroup),
-// so a wave's registers (queries, one output block, one score block) fit in
-// the 256 architectural VGPRs and two waves share each SIMD: one wave's
+// The window and page kernels run NW waves of 32 window rows each.  With 8
+// (256 rows per workgroup) a wave's registers (queries, one output block, one
+// score block) fit in 256 VGPRs and two waves share each SIMD: one wave's
 // softmax overlaps the other's MFMA.
+//
+// Each kernel has a body that works on one problem and two entries: one
+// problem given by value, or a batch in device memory with the problem in
+// blockIdx.z.  A single call takes 8 waves also where its rows need fewer:
+// its few workgroups are bound by the latency of their tiles, and the idle
+// waves help to stage them (40 window rows per KV head, 4224 tokens: window
+// kernel 11.1 us, 13.7 with 2 waves).  A batch of such problems has
+// workgroups to spare and takes 2 or 4 waves and one LDS buffer each, up to
+// four workgroups per compute unit.
 #include "ckv_device.h"
 #include "ckv_kernels.h"
 
@@ -30,8 +39,14 @@
 
 namespace ckv {
 
-constexpr int kNW = 8;               // waves per workgroup
-constexpr int kRowsWG = 32 * kNW;    // window rows per workgroup
+constexpr int kNW = 8;               // waves per workgroup of the token mass, and NW at most
+// pages (or candidates) and (page, head) maxima of a page workgroup: with
+// 2 waves, four workgroups share a compute unit's LDS (40 KB each)
+constexpr int page_items_max(int nw) { return nw == kNW ? kPageItemsMax : 64; }
+constexpr int page_rmax_cap(int nw) { return nw == kNW ? kPageRmaxCap : 128 * nw; }
+// tile buffers in LDS: with two, a workgroup stages a tile beside the one it
+// works on; narrow workgroups leave that to the others of the compute unit
+constexpr int tile_buffers(int nw) { return nw == kNW ? 2 : 1; }
 // The running output is rescaled whenever a row's max grows (the wave skips
 // the rescale when no row's max grew), so the float16 weight of a row's
 // largest logit is exactly 1, as it is in the per-page pass (whose reference
@@ -322,21 +337,24 @@ __device__ __forceinline__ void pv_half(const _Float16* sV, int tb, int col, int
 // ---------------------------------------------------------------------------
 // A. split window attention
 // ---------------------------------------------------------------------------
-template <int D, bool PG>
-__global__ __launch_bounds__(kNW * 64, 1) void window_attention_kernel(AttnGeom a, AttnSplit sp) {
-  constexpr int NT = kNW * 64, KS = D / 16, DB = D / 32;
+// Splits [split, split1) of row block rblk of KV head g.  MULTI: there may be
+// several; their tiles form one stream, so that the next split's loads cover
+// the end of the one before and the prologue is paid once.
+template <int D, bool PG, int NW, bool MULTI>
+__device__ __forceinline__ void window_attention_body(const AttnGeom& a, const AttnSplit& sp, int split, int split1,
+                                                      int rblk, int g) {
+  constexpr int NT = NW * 64, KS = D / 16, DB = D / 32, kRowsWG = 32 * NW, NBUF = tile_buffers(NW);
   using St = Stager<D, NT, PG>;
-  __shared__ __align__(16) uint16_t sK[2][kTile * St::KP];
-  __shared__ __align__(16) _Float16 sV[2][D * St::VP];
-  __shared__ __align__(16) int sP[2][kTile];
-  __shared__ int sFull[2][2];
+  __shared__ __align__(16) uint16_t sK[NBUF][kTile * St::KP];
+  __shared__ __align__(16) _Float16 sV[NBUF][D * St::VP];
+  __shared__ __align__(16) int sP[NBUF][kTile];
+  __shared__ int sFull[NBUF][2];
   __shared__ int sMin;
 
-  const int g = blockIdx.z, split = blockIdx.x, rblk = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, col = lane & 31;
   const int t_begin = split * sp.chunk;
-  const int t_end = min(a.S, t_begin + sp.chunk);
+  const int t_end = min(a.S, MULTI ? split1 * sp.chunk : t_begin + sp.chunk);
   const uint16_t* kh = a.k + (int64_t)g * a.kv_head_stride;
   const uint16_t* vh = a.v + (int64_t)g * a.kv_head_stride;
 
@@ -420,46 +438,92 @@ __global__ __launch_bounds__(kNW * 64, 1) void window_attention_kernel(AttnGeom 
       pv_slot<D, St::VP>(sV[b], 1, col, half, h[1], oacc);
     }
   };
-  St stA, stB;
-  issue(stA, 0);
-  issue(stB, 1);
-  if (n_tiles > 0) stA.commit(sK[0], sV[0], sP[0], sFull[0], minq, tid);
-  __syncthreads();
-  for (int it = 0; it < n_tiles; it += 2) {
-    issue(stA, it + 2);
-    compute(0, it);
-    if (it + 1 < n_tiles) stB.commit(sK[1], sV[1], sP[1], sFull[1], minq, tid);
-    __syncthreads();
-    if (it + 1 >= n_tiles) break;
-    issue(stB, it + 3);
-    compute(1, it + 1);
-    if (it + 2 < n_tiles) stA.commit(sK[0], sV[0], sP[0], sFull[0], minq, tid);
-    __syncthreads();
-  }
-
-  // partial results of this split (m in log2 units, output relative to it)
-  const float lt = sum32(l);
-  const int ct = sum32i(cnt);
-  if (!ri.ok) return;
-  const size_t idx = CKV_IDX((size_t)(g * sp.n_splits + split) * sp.rows_pad + ri.row,
-                             (int64_t)a.Hkv * sp.n_splits * sp.rows_pad, a.dbg, 1);
-  if (half == 0) {
-    sp.part_m[idx] = mref;
-    sp.part_l[idx] = lt;
-    sp.part_c[idx] = ct;
-    sp.part_t[idx] = mt;
-    sp.part_p[idx] = mp;
-  }
-  float* po = sp.part_o + idx * D;
-#pragma unroll
-  for (int db = 0; db < DB; ++db)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      f32x4 v4;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) v4[j] = oacc[db][4 * i + j];
-      *reinterpret_cast<f32x4*>(po + 32 * db + 8 * i + 4 * half) = v4;
+  // partial results of a split (m in log2 units, output relative to it)
+  auto store = [&](int split) {
+    const float lt = sum32(l);
+    const int ct = sum32i(cnt);
+    if (!ri.ok) return;
+    const size_t idx = CKV_IDX((size_t)(g * sp.n_splits + split) * sp.rows_pad + ri.row,
+                               (int64_t)a.Hkv * sp.n_splits * sp.rows_pad, a.dbg, 1);
+    if (half == 0) {
+      sp.part_m[idx] = mref;
+      sp.part_l[idx] = lt;
+      sp.part_c[idx] = ct;
+      sp.part_t[idx] = mt;
+      sp.part_p[idx] = mp;
     }
+    float* po = sp.part_o + idx * D;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        f32x4 v4;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v4[j] = oacc[db][4 * i + j];
+        *reinterpret_cast<f32x4*>(po + 32 * db + 8 * i + 4 * half) = v4;
+      }
+  };
+  // MULTI: after the last tile of a split, its results go out and the state restarts
+  const int split_tiles = MULTI ? sp.chunk / kTile : n_tiles;
+  auto end_tile = [&](int it) {
+    if (!MULTI || ((it + 1) % split_tiles != 0 && it + 1 < n_tiles)) return;
+    store(split + it / split_tiles);
+#pragma unroll
+    for (int db = 0; db < DB; ++db) oacc[db] = zero16();
+    mref = mp = -INFINITY;
+    l = 0.f;
+    cnt = 0;
+    mt = -1;
+  };
+  St stA;
+  issue(stA, 0);
+  if constexpr (NBUF == 1) {
+    for (int it = 0; it < n_tiles; ++it) {
+      stA.commit(sK[0], sV[0], sP[0], sFull[0], minq, tid);
+      __syncthreads();
+      issue(stA, it + 1);
+      compute(0, it);
+      end_tile(it);
+      __syncthreads();
+    }
+  } else {
+    St stB;
+    issue(stB, 1);
+    if (n_tiles > 0) stA.commit(sK[0], sV[0], sP[0], sFull[0], minq, tid);
+    __syncthreads();
+    for (int it = 0; it < n_tiles; it += 2) {
+      issue(stA, it + 2);
+      compute(0, it);
+      end_tile(it);
+      if (it + 1 < n_tiles) stB.commit(sK[1], sV[1], sP[1], sFull[1], minq, tid);
+      __syncthreads();
+      if (it + 1 >= n_tiles) break;
+      issue(stB, it + 3);
+      compute(1, it + 1);
+      end_tile(it + 1);
+      if (it + 2 < n_tiles) stA.commit(sK[0], sV[0], sP[0], sFull[0], minq, tid);
+      __syncthreads();
+    }
+  }
+  if (!MULTI) store(split);
+}
+
+template <int D, bool PG>
+__global__ __launch_bounds__(kNW * 64, 1) void window_attention_kernel(AttnGeom a, AttnSplit sp) {
+  window_attention_body<D, PG, kNW, false>(a, sp, blockIdx.x, blockIdx.x + 1, blockIdx.y, blockIdx.z);
+}
+
+// blockIdx.x: group of p.splits_per_block splits; blockIdx.y: row block
+// (fastest) and KV head
+template <int D, bool PG, int NW>
+__global__ __launch_bounds__(NW * 64, 2) void window_attention_batch(const MeasureProb* __restrict__ probs) {
+  const MeasureProb& p = probs[blockIdx.z];
+  const AttnGeom a = p.a;
+  const AttnSplit sp = p.sp;
+  const int nrb = (a.rows + 32 * NW - 1) / (32 * NW), g = blockIdx.y / nrb;
+  const int s0 = blockIdx.x * p.splits_per_block;
+  if (s0 >= sp.n_splits || g >= a.Hkv) return;
+  window_attention_body<D, PG, NW, true>(a, sp, s0, min(sp.n_splits, s0 + p.splits_per_block), blockIdx.y % nrb, g);
 }
 
 // Merge of the splits: D/4 lanes per window row (16 bytes of the partial
@@ -471,15 +535,15 @@ __global__ __launch_bounds__(kNW * 64, 1) void window_attention_kernel(AttnGeom 
 constexpr int kCombBatch = 16;
 
 template <int D>
-__global__ __launch_bounds__(256) void combine_kernel(AttnGeom a, AttnSplit sp, RowStats rs,
-                                                      float* lse_out, ZeroList zl) {
+__device__ __forceinline__ void combine_body(const AttnGeom& a, const AttnSplit& sp, const RowStats& rs,
+                                             float* lse_out, const ZeroList& zl, int bx, int nbx) {
   constexpr int TPR = D / 4;          // lanes per row
   constexpr int RPW = 64 / TPR;       // rows per wave
   const int lane = threadIdx.x & 63, c = lane % TPR;
-  const int wid = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int wid = bx * 4 + (threadIdx.x >> 6);
   // zero the outputs that later kernels reduce into with atomic max
-  const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t gsz = (size_t)gridDim.x * blockDim.x;
+  const size_t gid = (size_t)bx * blockDim.x + threadIdx.x;
+  const size_t gsz = (size_t)nbx * blockDim.x;
   for (size_t i = gid; i < zl.n0; i += gsz) zl.p0[i] = 0.f;
   for (size_t i = gid; i < zl.n1; i += gsz) zl.p1[i] = 0.f;
   for (size_t i = gid; i < zl.n2; i += gsz) zl.p2[i] = 0.f;
@@ -559,6 +623,22 @@ __global__ __launch_bounds__(256) void combine_kernel(AttnGeom a, AttnSplit sp, 
   }
 }
 
+template <int D>
+__global__ __launch_bounds__(256) void combine_kernel(AttnGeom a, AttnSplit sp, RowStats rs, float* lse_out,
+                                                      ZeroList zl) {
+  combine_body<D>(a, sp, rs, lse_out, zl, blockIdx.x, gridDim.x);
+}
+
+template <int D>
+__global__ __launch_bounds__(256) void combine_batch(const MeasureProb* __restrict__ probs) {
+  const MeasureProb& p = probs[blockIdx.z];
+  const AttnGeom a = p.a;
+  const AttnSplit sp = p.sp;
+  const RowStats rs = p.rs;
+  const ZeroList zl = p.zl;
+  combine_body<D>(a, sp, rs, p.lse_out, zl, blockIdx.x, gridDim.x);
+}
+
 // ---------------------------------------------------------------------------
 // B. per-page deletion effect (MODE 0) or per-candidate residual (MODE 1)
 //
@@ -568,14 +648,19 @@ __global__ __launch_bounds__(256) void combine_kernel(AttnGeom a, AttnSplit sp, 
 // ---------------------------------------------------------------------------
 // NB: 32-token slots a page may span (1 when every page has <= 32 tokens).
 constexpr int kAcrossSplit = 0x7f;   // page class: across a split boundary of the window pass
-template <int D, int MODE, int NB, bool PG>
-__global__ __launch_bounds__(kNW * 64, 1) void page_kernel(AttnGeom a, PageWork pw, RowStats rs) {
-  constexpr int NT = kNW * 64, KS = D / 16, DB = D / 32;
+// SG: 2 when the rows need at most half of the workgroup's waves: the waves
+// then form two groups of the same rows, one per page of a tile.
+template <int D, int MODE, int NB, bool PG, int NW, int SG>
+__device__ __forceinline__ void page_body(const AttnGeom& a, const PageWork& pw, const RowStats& rs, int bx, int nbx,
+                                          int rblk, int g) {
+  constexpr int NT = NW * 64, KS = D / 16, DB = D / 32, NBUF = tile_buffers(NW);
+  constexpr int RW = NW / SG, kRowsWG = 32 * RW;   // waves across the rows
+  constexpr int kPageItemsMax = page_items_max(NW), kPageRmaxCap = page_rmax_cap(NW);
   using St = Stager<D, NT, PG>;
-  __shared__ __align__(16) uint16_t sK[2][kTile * St::KP];
-  __shared__ __align__(16) _Float16 sV[2][D * St::VP];
-  __shared__ __align__(16) int sP[2][kTile];
-  __shared__ int sFull[2][2];
+  __shared__ __align__(16) uint16_t sK[NBUF][kTile * St::KP];
+  __shared__ __align__(16) _Float16 sV[NBUF][D * St::VP];
+  __shared__ __align__(16) int sP[NBUF][kTile];
+  __shared__ int sFull[NBUF][2];
   // MODE 0: per (page of the block, local head) maximum ratio, flushed to
   // global memory once after the last tile, so the tile loop issues no
   // global atomics (a wave that waits on them stalls the whole workgroup at
@@ -593,20 +678,18 @@ __global__ __launch_bounds__(kNW * 64, 1) void page_kernel(AttnGeom a, PageWork 
   __shared__ int sTileIt[kPageItemsMax + 1];  // per tile: first item; entry n_tiles = i_end
   __shared__ int sNTiles;
 
-  const int g = blockIdx.z, rblk = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, col = lane & 31;
   int n_items = pw.n_items;
   if (MODE == 1) n_items = min(*pw.n_cand, pw.n_items);
-  if (MODE == 1 && pw.clear && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)
+  if (MODE == 1 && pw.clear && bx == 0 && rblk == 0 && g == 0)
     for (int i = tid; i < pw.n_clear; i += NT) pw.clear[i] = 0;
-  // MODE 0: a run of pages.  MODE 1: every gridDim.x-th candidate, since the
+  // MODE 0: a run of pages.  MODE 1: every nbx-th candidate, since the
   // host knows only a bound of their number (34 candidates under a bound of
   // 256 on 256 workgroups: 46 us with runs of 8, which left 5 of 32 blocks
   // with work, 23 us spread)
-  const int i_begin = MODE == 0 ? (int)blockIdx.x * pw.items_per_block : 0;
-  const int i_end = MODE == 0 ? min(n_items, i_begin + pw.items_per_block)
-                              : (n_items - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
+  const int i_begin = MODE == 0 ? bx * pw.items_per_block : 0;
+  const int i_end = MODE == 0 ? min(n_items, i_begin + pw.items_per_block) : (n_items - bx + nbx - 1) / nbx;
   if (i_begin >= i_end) return;
   const uint16_t* kh = a.k + (int64_t)g * a.kv_head_stride;
   const uint16_t* vh = a.v + (int64_t)g * a.kv_head_stride;
@@ -615,7 +698,7 @@ __global__ __launch_bounds__(kNW * 64, 1) void page_kernel(AttnGeom a, PageWork 
   // on a global load inside the loop (a wait there would also drain the
   // loads issued ahead); an invalid candidate index is an empty page
   for (int i = tid; i < i_end - i_begin; i += NT) {
-    const int pg = MODE == 0 ? i_begin + i : pw.cand[blockIdx.x + i * gridDim.x];
+    const int pg = MODE == 0 ? i_begin + i : pw.cand[bx + i * nbx];
     const bool ok = pg >= 0 && pg < pw.n_pages;
     sItStart[i] = ok ? pw.start[pg] : 0;
     // the length, and above bit 8 (MODE 0) where the page meets the window
@@ -630,7 +713,7 @@ __global__ __launch_bounds__(kNW * 64, 1) void page_kernel(AttnGeom a, PageWork 
     }
     sItLen[i] = lw;
   }
-  const RowInfo ri = row_info(a, g, rblk * kRowsWG + wave * 32 + col);
+  const RowInfo ri = row_info(a, g, rblk * kRowsWG + (wave % RW) * 32 + col);
   const bool wave_on = __ballot(ri.ok) != 0ull;
   const int minq = block_min_qpos(ri, &sMin);    // its barriers also publish the page spans
   bf16x8 qf[KS];
@@ -705,7 +788,7 @@ __global__ __launch_bounds__(kNW * 64, 1) void page_kernel(AttnGeom a, PageWork 
   // page `item` of the tile in buffer b, at slot ps (a constant at each call,
   // so the slot's LDS offsets fold into the instructions)
   auto page = [&](int b, int item, int m, const int ps) {
-    const int t_cand = blockIdx.x + item * gridDim.x;   // MODE 1: the candidate
+    const int t_cand = bx + item * nbx;   // MODE 1: the candidate
     {
       const int lw = sItLen[item - i_begin];
       const int len = lw & 0xff, cross = lw >> 8;
@@ -860,15 +943,25 @@ __global__ __launch_bounds__(kNW * 64, 1) void page_kernel(AttnGeom a, PageWork 
   };
   auto process = [&](int b, int it, int m) {
     if (!wave_on) return;
-    page(b, it, m, 0);
-    if (m == 2) page(b, it + 1, m, 1);
+    if (SG == 1 || wave < RW) page(b, it, m, 0);
+    if (m == 2 && (SG == 1 || wave >= RW)) page(b, it + 1, m, 1);
   };
 
   St st;
   issue_tile(st, 0);
-  st.commit(sK[0], sV[0], sP[0], sFull[0], minq, tid);
-  __syncthreads();
+  if constexpr (NBUF == 2) {
+    st.commit(sK[0], sV[0], sP[0], sFull[0], minq, tid);
+    __syncthreads();
+  }
   for (int k = 0; k < n_tiles; ++k) {
+    if constexpr (NBUF == 1) {
+      const int t_cur = sTileIt[k], m = sTileIt[k + 1] - t_cur;
+      st.commit(sK[0], sV[0], sP[0], sFull[0], minq, tid);
+      __syncthreads();
+      issue_tile(st, k + 1);
+      process(0, t_cur, m);
+      __syncthreads();
+    } else {
     const int b = k & 1;
     const int t_cur = sTileIt[k], m = sTileIt[k + 1] - t_cur;
     issue_tile(st, k + 1);
@@ -877,6 +970,7 @@ __global__ __launch_bounds__(kNW * 64, 1) void page_kernel(AttnGeom a, PageWork 
     // buffer, so no path leaves a load outstanding into the next iteration
     st.commit(sK[b ^ 1], sV[b ^ 1], sP[b ^ 1], sFull[b ^ 1], minq, tid);
     __syncthreads();
+    }
   }
   if (MODE == 0) {
     // Eq. (7): maxima over the block's rows, per head and over heads
@@ -904,6 +998,23 @@ __global__ __launch_bounds__(kNW * 64, 1) void page_kernel(AttnGeom a, PageWork 
       }
     }
   }
+}
+
+template <int D, int MODE, int NB, bool PG, int SG>
+__global__ __launch_bounds__(kNW * 64, 1) void page_kernel(AttnGeom a, PageWork pw, RowStats rs) {
+  page_body<D, MODE, NB, PG, kNW, SG>(a, pw, rs, blockIdx.x, gridDim.x, blockIdx.y, blockIdx.z);
+}
+
+template <int D, int NB, bool PG, int NW, int SG>
+__global__ __launch_bounds__(NW * 64, 2) void page_batch(const MeasureProb* __restrict__ probs) {
+  constexpr int kRowsWG = 32 * NW / SG;
+  const MeasureProb& p = probs[blockIdx.z];
+  const AttnGeom a = p.a;
+  const PageWork pw = p.pw;
+  const RowStats rs = p.rs;
+  const int nrb = (a.rows + kRowsWG - 1) / kRowsWG, g = blockIdx.y / nrb;
+  if (g >= a.Hkv) return;
+  page_body<D, 0, NB, PG, NW, SG>(a, pw, rs, blockIdx.x, gridDim.x, blockIdx.y % nrb, g);
 }
 
 // ---------------------------------------------------------------------------
@@ -1110,11 +1221,13 @@ __device__ __forceinline__ int rescaled_entry(const AttnSplit& sp, const RowStat
   return min(max(mt - st, 0), ln);
 }
 
-// the fix-up of block bx of nb fix-up blocks, each of T threads
+// The fix-up of block bx of nb fix-up blocks, each of T threads.  The parts of
+// a pair follow from nb_parts, the same for one problem and for a batch,
+// whatever number of blocks serves them.
 template <int D, bool PG, int T>
 __device__ __forceinline__ void page_fixup_body(const AttnGeom& a, const AttnSplit& sp, const RowStats& rs,
                                                 const PageWork& pw, float* fpart, int* arrive, int parts,
-                                                int item_budget, int bx, int nb) {
+                                                int item_budget, int bx, int nb, int nb_parts) {
   constexpr int TPR = D / 8;                  // threads per token row (16 bytes each)
   constexpr int RPR = T / TPR;                // token rows per round
   constexpr int UNR = 128 / RPR;              // rounds whose loads are in flight together
@@ -1122,7 +1235,7 @@ __device__ __forceinline__ void page_fixup_body(const AttnGeom& a, const AttnSpl
   __shared__ int sLast;
   const int tid = threadIdx.x, c = tid % TPR, r = tid / TPR;
   const int n = min(*pw.fix_count, pw.fix_cap);
-  parts = fix_parts(parts, item_budget, n, nb, sp.chunk, pw.fix_cap);
+  parts = fix_parts(parts, item_budget, n, nb_parts, sp.chunk, pw.fix_cap);
   for (int item = bx; item < n * parts; item += nb) {
     const int e = item / parts, part = item % parts;
     // entry: page, global row, page start, page length
@@ -1226,7 +1339,18 @@ __device__ __forceinline__ void page_fixup_body(const AttnGeom& a, const AttnSpl
 template <int D, bool PG>
 __global__ __launch_bounds__(kFixT) void page_fixup_kernel(AttnGeom a, AttnSplit sp, RowStats rs, PageWork pw,
                                                            float* fpart, int* arrive, int parts, int item_budget) {
-  page_fixup_body<D, PG, kFixT>(a, sp, rs, pw, fpart, arrive, parts, item_budget, blockIdx.x, gridDim.x);
+  page_fixup_body<D, PG, kFixT>(a, sp, rs, pw, fpart, arrive, parts, item_budget, blockIdx.x, gridDim.x, gridDim.x);
+}
+
+template <int D, bool PG>
+__global__ __launch_bounds__(kFixT) void page_fixup_batch(const MeasureProb* __restrict__ probs, int parts) {
+  const MeasureProb& p = probs[blockIdx.z];
+  const AttnGeom a = p.a;
+  const AttnSplit sp = p.sp;
+  const RowStats rs = p.rs;
+  const PageWork pw = p.pw;
+  page_fixup_body<D, PG, kFixT>(a, sp, rs, pw, p.fpart, p.arrive, parts, 0, blockIdx.x, gridDim.x,
+                                max(1, min(pw.fix_cap * parts, kFixGrid)));
 }
 
 // ---------------------------------------------------------------------------
@@ -1242,8 +1366,8 @@ constexpr int kMassMaxRows = 2048;   // window rows per KV head the mass kernel 
 constexpr int kMassMaxPairs = kMassMaxRows / 32;
 
 template <int D, bool PG>
-__global__ __launch_bounds__(kNW * 64) void token_mass_kernel(AttnGeom a, RowStats rs, float* mass,
-                                                              int chunk) {
+__device__ __forceinline__ void token_mass_general(const AttnGeom& a, const RowStats& rs, float* mass, int chunk,
+                                                   int bx, int g) {
   constexpr int NT = kNW * 64, KS = D / 16;
   constexpr int KP = D + 8, CPR = D / 8, KCH = kTile * CPR, KPT = (KCH + NT - 1) / NT;
   __shared__ __align__(16) uint16_t sK[2][kTile * KP];
@@ -1251,10 +1375,9 @@ __global__ __launch_bounds__(kNW * 64) void token_mass_kernel(AttnGeom a, RowSta
   __shared__ float sPart[kMassMaxPairs][kTile];
   __shared__ float sL2[kMassMaxRows];
   __shared__ int sQP[kMassMaxRows];
-  const int g = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, col = lane & 31;
-  const int t_begin = blockIdx.x * chunk;
+  const int t_begin = bx * chunk;
   const int t_end = min(a.S, t_begin + chunk);
   if (t_begin >= t_end) return;
   const uint16_t* kh = a.k + (int64_t)g * a.kv_head_stride;
@@ -1344,6 +1467,11 @@ __global__ __launch_bounds__(kNW * 64) void token_mass_kernel(AttnGeom a, RowSta
     }
     __syncthreads();
   }
+}
+
+template <int D, bool PG>
+__global__ __launch_bounds__(kNW * 64) void token_mass_kernel(AttnGeom a, RowStats rs, float* mass, int chunk) {
+  token_mass_general<D, PG>(a, rs, mass, chunk, blockIdx.x, blockIdx.y);
 }
 
 // The same with every (query head, 32-row block) pair of the workgroup owned
@@ -1523,25 +1651,60 @@ __global__ __launch_bounds__(kNW * 64) void mass_fixup_kernel(AttnGeom a, AttnSp
                                                               float* fpart, int* arrive, int parts, float* mass,
                                                               int chunk, int nfix, int mx, int my) {
   if ((int)blockIdx.x < nfix) {
-    page_fixup_body<D, PG, kNW * 64>(a, sp, rs, pw, fpart, arrive, parts, 0, blockIdx.x, nfix);
+    page_fixup_body<D, PG, kNW * 64>(a, sp, rs, pw, fpart, arrive, parts, 0, blockIdx.x, nfix, nfix);
     return;
   }
   const int b = blockIdx.x - nfix;
   token_mass_body<D, PPW, PG>(a, rs, mass, chunk, b % mx, (b / mx) % my, b / (mx * my));
 }
 
+// The same over a batch: `nfix` fix-up blocks per problem serve the parts that
+// the single call's kMassFixBlocks blocks would take (problems without pages
+// have an empty list), then the problem's token-mass grid.
+template <int D, int PPW, bool PG>
+__global__ __launch_bounds__(kNW * 64) void mass_fixup_batch(const MeasureProb* __restrict__ probs, int parts, int nfix,
+                                                             int mx, int nz) {
+  const MeasureProb& p = probs[blockIdx.z];
+  const AttnGeom a = p.a;
+  const RowStats rs = p.rs;
+  if ((int)blockIdx.x < nfix) {
+    const AttnSplit sp = p.sp;
+    const PageWork pw = p.pw;
+    if (pw.n_pages > 0)
+      page_fixup_body<D, PG, kNW * 64>(a, sp, rs, pw, p.fpart, p.arrive, parts, 0, blockIdx.x, nfix, kMassFixBlocks);
+    return;
+  }
+  const int b = blockIdx.x - nfix, g = b / mx / nz;
+  if (g < a.Hkv) token_mass_body<D, PPW, PG>(a, rs, p.mass, p.mass_chunk, b % mx, g, b / mx % nz);
+}
+
+template <int D, bool PG>
+__global__ __launch_bounds__(kNW * 64) void token_mass_batch(const MeasureProb* __restrict__ probs) {
+  const MeasureProb& p = probs[blockIdx.z];
+  const AttnGeom a = p.a;
+  const RowStats rs = p.rs;
+  if ((int)blockIdx.y < a.Hkv) token_mass_general<D, PG>(a, rs, p.mass, p.mass_chunk, blockIdx.x, blockIdx.y);
+}
 
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-int rows_per_block_attention() { return kRowsWG; }
-int rows_per_block_page() { return kRowsWG; }
-int page_heads_per_block(int W, int group) { return std::min(group, (kRowsWG - 1) / W + 2); }
+// Waves per window or page workgroup of a batch, a block of 32 rows each: 4 up
+// to 128 rows (with 2 waves for up to 64 rows the tile stager spills and a
+// batch of 40 problems of 4224 tokens takes 588 us instead of 487), else 8.
+int batch_waves(int rows) { return rows <= 128 ? 4 : kNW; }
+// Row groups of a page workgroup of nw waves: two, one per page of a tile,
+// where the rows leave half of the waves idle.
+int page_row_groups(int nw, int rows) { return rows <= 16 * nw ? 2 : 1; }
+int max_waves() { return kNW; }
+int page_items_limit(int nw, int W, int group) {
+  const int heads = std::min(group, (32 * nw - 1) / W + 2);
+  return std::min(page_items_max(nw), page_rmax_cap(nw) / heads);
+}
 int token_mass_max_rows() { return kMassMaxRows; }
 
 hipError_t launch_window_attention(const AttnGeom& a, const AttnSplit& sp, hipStream_t s) {
-  const int nrb = (a.rows + kRowsWG - 1) / kRowsWG;
-  dim3 grid(sp.n_splits, nrb, a.Hkv), block(kNW * 64);
+  dim3 grid(sp.n_splits, (a.rows + 32 * kNW - 1) / (32 * kNW), a.Hkv), block(kNW * 64);
   const bool pg = a.slot != nullptr;
   if (a.D == 128) {
     if (pg) hipLaunchKernelGGL((window_attention_kernel<128, true>), grid, block, 0, s, a, sp);
@@ -1553,10 +1716,14 @@ hipError_t launch_window_attention(const AttnGeom& a, const AttnSplit& sp, hipSt
   return hipGetLastError();
 }
 
+int combine_blocks(const AttnGeom& a) {
+  const int waves = (a.Hkv * a.rows * a.D + 255) / 256;   // 256 / D rows per wave
+  return (waves + 3) / 4;
+}
+
 hipError_t launch_combine(const AttnGeom& a, const AttnSplit& sp, const RowStats& rs, float* lse_out,
                           const ZeroList& zl, hipStream_t s) {
-  const int waves = (a.Hkv * a.rows * a.D + 255) / 256;   // 256 / D rows per wave
-  dim3 grid((waves + 3) / 4), block(256);
+  dim3 grid(combine_blocks(a)), block(256);
   if (a.D == 128) hipLaunchKernelGGL((combine_kernel<128>), grid, block, 0, s, a, sp, rs, lse_out, zl);
   else hipLaunchKernelGGL((combine_kernel<64>), grid, block, 0, s, a, sp, rs, lse_out, zl);
   return hipGetLastError();
@@ -1564,31 +1731,100 @@ hipError_t launch_combine(const AttnGeom& a, const AttnSplit& sp, const RowStats
 
 hipError_t launch_page_kernel(const AttnGeom& a, const PageWork& pw, const RowStats& rs, int mode,
                               int max_len, hipStream_t s) {
-  const int nrb = (a.rows + kRowsWG - 1) / kRowsWG;
   const int nblk = (pw.n_items + pw.items_per_block - 1) / pw.items_per_block;
   if (nblk == 0) return hipSuccess;
-  dim3 grid(nblk, nrb, a.Hkv), block(kNW * 64);
+  dim3 grid(nblk, (a.rows + 32 * kNW - 1) / (32 * kNW), a.Hkv), block(kNW * 64);
   const bool two = max_len > 32, pg = a.slot != nullptr;
-#define CKV_PAGE_LAUNCH(DD, MM)                                                                   \
-  do {                                                                                            \
-    if (pg) {                                                                                     \
-      if (two) hipLaunchKernelGGL((page_kernel<DD, MM, 2, true>), grid, block, 0, s, a, pw, rs);  \
-      else hipLaunchKernelGGL((page_kernel<DD, MM, 1, true>), grid, block, 0, s, a, pw, rs);      \
-    } else {                                                                                      \
-      if (two) hipLaunchKernelGGL((page_kernel<DD, MM, 2, false>), grid, block, 0, s, a, pw, rs); \
-      else hipLaunchKernelGGL((page_kernel<DD, MM, 1, false>), grid, block, 0, s, a, pw, rs);     \
-    }                                                                                             \
+  // the residual pass is bound by its stores and takes one form
+  const bool sg2 = mode == 0 && page_row_groups(kNW, a.rows) == 2;
+#define CKV_PAGE_LAUNCH(DD, MM, SS)                                                                   \
+  do {                                                                                                \
+    if (pg) {                                                                                         \
+      if (two) hipLaunchKernelGGL((page_kernel<DD, MM, 2, true, SS>), grid, block, 0, s, a, pw, rs);  \
+      else hipLaunchKernelGGL((page_kernel<DD, MM, 1, true, SS>), grid, block, 0, s, a, pw, rs);      \
+    } else {                                                                                          \
+      if (two) hipLaunchKernelGGL((page_kernel<DD, MM, 2, false, SS>), grid, block, 0, s, a, pw, rs); \
+      else hipLaunchKernelGGL((page_kernel<DD, MM, 1, false, SS>), grid, block, 0, s, a, pw, rs);     \
+    }                                                                                                 \
   } while (0)
   if (a.D == 128) {
-    if (mode == 0) CKV_PAGE_LAUNCH(128, 0);
-    else CKV_PAGE_LAUNCH(128, 1);
+    if (mode == 1) CKV_PAGE_LAUNCH(128, 1, 1);
+    else if (sg2) CKV_PAGE_LAUNCH(128, 0, 2);
+    else CKV_PAGE_LAUNCH(128, 0, 1);
   } else {
-    if (mode == 0) CKV_PAGE_LAUNCH(64, 0);
-    else CKV_PAGE_LAUNCH(64, 1);
+    if (mode == 1) CKV_PAGE_LAUNCH(64, 1, 1);
+    else if (sg2) CKV_PAGE_LAUNCH(64, 0, 2);
+    else CKV_PAGE_LAUNCH(64, 0, 1);
   }
 #undef CKV_PAGE_LAUNCH
   return hipGetLastError();
 }
+
+// a launch over the instantiations of <head width, paged>
+#define CKV_DP(KERN, ...)                                                                         \
+  do {                                                                                            \
+    if (D == 128) { if (pg) KERN(128, true, __VA_ARGS__); else KERN(128, false, __VA_ARGS__); }   \
+    else { if (pg) KERN(64, true, __VA_ARGS__); else KERN(64, false, __VA_ARGS__); }              \
+  } while (0)
+
+// The kernels of a batch of problems that agree in head width, paging, waves
+// per block, page kind and token-mass form (see MeasureBatch): one launch
+// each over every problem.
+hipError_t launch_measure_batch(const MeasureProb* dev, const MeasureBatch& b, int kernel, hipStream_t s) {
+  const int nw = b.nw, D = b.D;
+  const bool pg = b.paged;
+  if (kernel == 0) {
+    dim3 grid(b.max_split_groups, b.max_rb_heads, b.n), block(nw * 64);
+#define CKV_K(DD, PP, WW) hipLaunchKernelGGL((window_attention_batch<DD, PP, WW>), grid, block, 0, s, dev)
+    if (nw == 4) CKV_DP(CKV_K, 4);
+    else CKV_DP(CKV_K, 8);
+#undef CKV_K
+  } else if (kernel == 1) {
+    dim3 grid(b.max_combine, 1, b.n), block(256);
+    if (D == 128) hipLaunchKernelGGL((combine_batch<128>), grid, block, 0, s, dev);
+    else hipLaunchKernelGGL((combine_batch<64>), grid, block, 0, s, dev);
+  } else if (kernel == 2) {
+    dim3 grid(b.max_page_blocks, b.max_rb_heads, b.n), block(nw * 64);
+#define CKV_K(DD, PP, NN, WW, SS) hipLaunchKernelGGL((page_batch<DD, NN, PP, WW, SS>), grid, block, 0, s, dev)
+    if (nw == 4 && b.page_groups == 2) { if (b.two) CKV_DP(CKV_K, 2, 4, 2); else CKV_DP(CKV_K, 1, 4, 2); }
+    else if (nw == 4) { if (b.two) CKV_DP(CKV_K, 2, 4, 1); else CKV_DP(CKV_K, 1, 4, 1); }
+    else { if (b.two) CKV_DP(CKV_K, 2, 8, 1); else CKV_DP(CKV_K, 1, 8, 1); }
+#undef CKV_K
+  } else if (kernel == 3) {
+    dim3 grid(b.fix_blocks, 1, b.n), block(kFixT);
+    if (D == 128) {
+      if (pg) hipLaunchKernelGGL((page_fixup_batch<128, true>), grid, block, 0, s, dev, kFixParts);
+      else hipLaunchKernelGGL((page_fixup_batch<128, false>), grid, block, 0, s, dev, kFixParts);
+    } else {
+      if (pg) hipLaunchKernelGGL((page_fixup_batch<64, true>), grid, block, 0, s, dev, kFixParts);
+      else hipLaunchKernelGGL((page_fixup_batch<64, false>), grid, block, 0, s, dev, kFixParts);
+    }
+  } else if (b.mass_ppw > 0) {
+    const int nfix = b.any_pages ? b.fix_blocks : 0;
+    dim3 grid(nfix + b.max_mass_x * b.max_heads * b.mass_nz, 1, b.n), block(kNW * 64);
+#define CKV_K(DD, PP, QQ) \
+  hipLaunchKernelGGL((mass_fixup_batch<DD, QQ, PP>), grid, block, 0, s, dev, kFixParts, nfix, b.max_mass_x, b.mass_nz)
+    if (D == 128) {
+      if (pg) { if (b.mass_ppw == 1) CKV_K(128, true, 1); else CKV_K(128, true, 2); }
+      else { if (b.mass_ppw == 1) CKV_K(128, false, 1); else CKV_K(128, false, 2); }
+    } else {
+      if (pg) { if (b.mass_ppw == 1) CKV_K(64, true, 1); else CKV_K(64, true, 2); }
+      else { if (b.mass_ppw == 1) CKV_K(64, false, 1); else CKV_K(64, false, 2); }
+    }
+#undef CKV_K
+  } else {
+    dim3 grid(b.max_mass_x, b.max_heads, b.n), block(kNW * 64);
+    if (D == 128) {
+      if (pg) hipLaunchKernelGGL((token_mass_batch<128, true>), grid, block, 0, s, dev);
+      else hipLaunchKernelGGL((token_mass_batch<128, false>), grid, block, 0, s, dev);
+    } else {
+      if (pg) hipLaunchKernelGGL((token_mass_batch<64, true>), grid, block, 0, s, dev);
+      else hipLaunchKernelGGL((token_mass_batch<64, false>), grid, block, 0, s, dev);
+    }
+  }
+  return hipGetLastError();
+}
+#undef CKV_DP
 
 hipError_t launch_page_fixup(const AttnGeom& a, const AttnSplit& sp, const RowStats& rs,
                              const PageWork& pw, float* fpart, int* arrive, int parts, int item_budget,
@@ -1606,18 +1842,24 @@ hipError_t launch_page_fixup(const AttnGeom& a, const AttnSplit& sp, const RowSt
   return hipGetLastError();
 }
 
-bool mass_fixup_applies(const AttnGeom& a) {
+// (query head, 32-row block) pairs per wave of the fast token-mass form, 0
+// for shapes whose heads do not fill whole workgroups
+int mass_pairs_per_wave(const AttnGeom& a) {
   const int nrb = (a.W + 31) / 32, n_pairs = a.group * nrb;
   const int ppw = n_pairs <= kNW ? 1 : 2;
-  return (kNW * ppw) % nrb == 0;
+  return (kNW * ppw) % nrb == 0 ? ppw : 0;
 }
+int mass_slices(const AttnGeom& a, int ppw) {
+  const int n_pairs = a.group * ((a.W + 31) / 32);
+  return (n_pairs + kNW * ppw - 1) / (kNW * ppw);
+}
+bool mass_fixup_applies(const AttnGeom& a) { return mass_pairs_per_wave(a) > 0; }
 
 hipError_t launch_mass_fixup(const AttnGeom& a, const AttnSplit& sp, const RowStats& rs, const PageWork& pw,
                              float* fpart, int* arrive, int parts, float* mass, int chunk, hipStream_t s) {
-  if (!mass_fixup_applies(a)) return hipErrorInvalidValue;
-  const int nrb = (a.W + 31) / 32, n_pairs = a.group * nrb;
-  const int ppw = n_pairs <= kNW ? 1 : 2;
-  const int nz = (n_pairs + kNW * ppw - 1) / (kNW * ppw);
+  const int ppw = mass_pairs_per_wave(a);
+  if (!ppw) return hipErrorInvalidValue;
+  const int nz = mass_slices(a, ppw);
   const int mx = (a.S + chunk - 1) / chunk, my = a.Hkv;
   const int nfix = kMassFixBlocks;
   dim3 grid(nfix + mx * my * nz), block(kNW * 64);
@@ -1642,12 +1884,10 @@ hipError_t launch_mass_fixup(const AttnGeom& a, const AttnSplit& sp, const RowSt
 
 hipError_t launch_token_mass(const AttnGeom& a, const RowStats& rs, float* mass, int chunk,
                              hipStream_t s) {
-  const int nrb = (a.W + 31) / 32, n_pairs = a.group * nrb;
-  const int ppw = n_pairs <= kNW ? 1 : 2;
+  const int ppw = mass_pairs_per_wave(a);
   const bool pg = a.slot != nullptr;
-  if ((kNW * ppw) % nrb == 0) {
-    const int nz = (n_pairs + kNW * ppw - 1) / (kNW * ppw);
-    dim3 grid((a.S + chunk - 1) / chunk, a.Hkv, nz), block(kNW * 64);
+  if (ppw) {
+    dim3 grid((a.S + chunk - 1) / chunk, a.Hkv, mass_slices(a, ppw)), block(kNW * 64);
 #define CKV_MASS_LAUNCH(DD, PP)                                                                       \
   do {                                                                                                \
     if (pg) hipLaunchKernelGGL((token_mass_fast<DD, PP, true>), grid, block, 0, s, a, rs, mass, chunk); \

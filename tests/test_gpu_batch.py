@@ -1,0 +1,95 @@
+"""ckv_measure_page_effects_batch over runs of problems that share their
+kernels (one launch each over the whole run): every output bit-identical to
+the single calls, whose results the oracle tests pin.
+
+The problems of a run differ in length (ragged last splits and tiles) and
+page lists; one has no pages, and a heavy key puts pairs on the fix-up list.
+The shapes are the edges of the batch's kernels: up to 64 rows per KV head
+(two page groups per workgroup), up to 128, above (8 waves), several row
+blocks; pages of at most 32 tokens and longer; contiguous and paged caches;
+the token mass in its fast and general forms.  Twelve problems of 32 splits
+and 8 KV heads give a workgroup several splits.
+"""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+WANT = ("R", "R_head", "o", "lse", "token_mass")
+
+
+@pytest.fixture(scope="module")
+def ckv():
+    import paper_2608_07855_amd as P
+    ctx = P.Context(0)
+    yield P, ctx
+    ctx.close()
+
+
+def _problem(P, hq, hkv, d, S, W, G, paged, seed, pages=True):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    rows = S + 300 if paged else S
+    k = torch.randn((hkv, rows, d), generator=g, device="cuda", dtype=torch.bfloat16)
+    v = torch.randn((hkv, rows, d), generator=g, device="cuda", dtype=torch.bfloat16)
+    q = torch.randn((hq, W, d), generator=g, device="cuda", dtype=torch.bfloat16)
+    slot = torch.randperm(rows, generator=g, device="cuda")[:S].to(torch.int32) if paged else None
+    for t in range(5, S, S // 7):     # keys that dominate some rows
+        k[:, int(slot[t]) if paged else t] *= 5
+    pos = torch.arange(S, dtype=torch.int32, device="cuda")
+    kv = P.kv_view(k, v, pos, S, slot=slot) if paged else P.kv_view(k, v, pos, S)
+    start = np.arange(3, S - W - G, G + 5, dtype=np.int32) if pages else np.zeros(0, np.int32)
+    rng = np.random.default_rng(seed)
+    length = rng.integers(max(1, G - 7), G + 1, len(start)).astype(np.int32)
+    return kv, P.window_view(q, pos[S - W:].clone()), P.Pages(start, length), (k, v, q, pos, slot)
+
+
+def _same(got, ref, what):
+    for i, (b, s) in enumerate(zip(got, ref)):
+        for key in WANT:
+            if b[key] is None:
+                assert s[key] is None or s[key].numel() == 0
+                continue
+            x, y = b[key].cpu().numpy().view(np.uint32), s[key].cpu().numpy().view(np.uint32)
+            assert np.array_equal(x, y), f"{what}: problem {i} {key}"
+
+
+@pytest.mark.parametrize("mass", [False, True])
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("hq,hkv,d,W,G", [(5, 1, 128, 8, 16), (4, 2, 64, 32, 48), (8, 2, 128, 32, 32),
+                                          (8, 2, 128, 29, 64), (8, 2, 64, 64, 24), (6, 2, 128, 100, 40),
+                                          (2, 1, 64, 80, 30)])
+def test_batch_is_the_single_calls(ckv, hq, hkv, d, W, G, paged, mass):
+    P, ctx = ckv
+    print(f"[batch] hq={hq} hkv={hkv} d={d} W={W} G={G} paged={paged} mass={mass}", flush=True)
+    want = WANT if mass else WANT[:-1]
+    pr = [_problem(P, hq, hkv, d, S, W, G, paged, seed=100 + i, pages=i != 2)
+          for i, S in enumerate((700, 1234, 900, 641, 2049))]
+    got = P.ckv_measure_page_effects_batch(ctx, [p[0] for p in pr], [p[1] for p in pr], [p[2] for p in pr], want=want)
+    ref = [P.ckv_measure_page_effects(ctx, p[0], p[1], p[2], want=want) for p in pr]
+    torch.cuda.synchronize()
+    ctx.sync()
+    _same(got, ref, "batch")
+
+
+def test_several_splits_per_workgroup_and_workspace_limit(ckv):
+    """Twelve problems in one launch; then with a workspace that holds one
+    problem only, where they go out one by one; then one that holds two."""
+    P, ctx0 = ckv
+    pr = [_problem(P, 16, 8, 64, 4096 - 60 * i, 8, 16, False, seed=i) for i in range(12)]
+    args = [[p[j] for p in pr] for j in range(3)]
+    ref = [P.ckv_measure_page_effects(ctx0, *p[:3], want=WANT) for p in pr]
+    _same(P.ckv_measure_page_effects_batch(ctx0, *args, want=WANT), ref, "no limit")
+    one = P.Context(0)
+    P.ckv_measure_page_effects(one, *pr[0][:3], want=WANT)
+    need = one.workspace_bytes()
+    one.close()
+    for limit in (need, 2 * need + 65536):
+        ctx = P.Context(0)
+        ctx.set_workspace_limit(limit)
+        got = P.ckv_measure_page_effects_batch(ctx, *args, want=WANT)
+        torch.cuda.synchronize()
+        assert ctx.workspace_bytes() <= limit
+        _same(got, ref, f"limit {limit}")
+        ctx.close()
