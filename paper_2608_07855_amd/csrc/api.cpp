@@ -765,7 +765,7 @@ int enqueue_measure(ckv_ctx* c, const AttnGeom& a, const MeasureBufs& b, const i
   if (n > 0) {
     const PageWork& pw = p.pw;
     CKV_LAUNCH(c, "page_effect", launch_page_kernel(a, pw, b.rs, 0, max_len, c->stream));
-    if (token_mass && mass_fixup_applies(a)) {
+    if (token_mass && mass_fixup_applies(a, mass_chunk(a))) {
       // the fix-up runs in the shadow of the token mass, in one launch
       CKV_LAUNCH(c, "token_mass_fixup", launch_mass_fixup(a, b.sp, b.rs, pw, b.fpart, b.arrive, ckv::kFixParts,
                                                           token_mass, mass_chunk(a), c->stream));
@@ -792,7 +792,8 @@ bool same_kernels(const BatchItem& x, const BatchItem& y) {
     return false;
   if (!x.mass) return true;
   const int ppw = mass_pairs_per_wave(x.a);
-  return ppw == mass_pairs_per_wave(y.a) && (ppw == 0 || mass_slices(x.a, ppw) == mass_slices(y.a, ppw));
+  return ppw == mass_pairs_per_wave(y.a) &&
+         mass_fixup_applies(x.a, mass_chunk(x.a)) == mass_fixup_applies(y.a, mass_chunk(y.a)) && (ppw == 0 || mass_slices(x.a, ppw) == mass_slices(y.a, ppw));
 }
 
 // Working memory of the problems one launch serves together, at most.  At
@@ -869,12 +870,12 @@ int enqueue_batch(ckv_ctx* c, const BatchItem* it, int n) {
   if ((rc = upload(c, blob.data(), blob.size(), dev))) return rc;
   CKV_LAUNCH(c, "window_attention", launch_measure_batch(dev, b, 0, c->stream));
   CKV_LAUNCH(c, "combine", launch_measure_batch(dev, b, 1, c->stream));
-  const bool fused = it[0].mass && b.mass_ppw > 0;
+  b.mass_fixup = b.any_pages && it[0].mass && mass_fixup_applies(it[0].a, mass_chunk(it[0].a));
   if (b.any_pages) {
     CKV_LAUNCH(c, "page_effect", launch_measure_batch(dev, b, 2, c->stream));
-    if (!fused) CKV_LAUNCH(c, "page_fixup", launch_measure_batch(dev, b, 3, c->stream));
+    if (!b.mass_fixup) CKV_LAUNCH(c, "page_fixup", launch_measure_batch(dev, b, 3, c->stream));
   }
-  if (it[0].mass) CKV_LAUNCH(c, fused && b.any_pages ? "token_mass_fixup" : "token_mass", launch_measure_batch(dev, b, 4, c->stream));
+  if (it[0].mass) CKV_LAUNCH(c, b.mass_fixup ? "token_mass_fixup" : "token_mass", launch_measure_batch(dev, b, 4, c->stream));
   return CKV_OK;
 }
 

@@ -162,10 +162,9 @@ hipError_t launch_page_fixup(const AttnGeom& a, const AttnSplit& sp, const RowSt
 // The same fix-up fused with the token mass of the same pass (one launch):
 // kMassFixBlocks blocks of 512 threads serve the listed pairs (grid-stride
 // over (pair, part) items), the rest of the grid is launch_token_mass's.
-// Applies unless the token mass needs its general kernel (window rows per KV
-// head that do not fill whole workgroups); otherwise the launcher refuses.
+// Applies where the token mass takes its fast form and leaves compute units idle.
 constexpr int kMassFixBlocks = 256;
-bool mass_fixup_applies(const AttnGeom& a);
+bool mass_fixup_applies(const AttnGeom& a, int chunk);
 hipError_t launch_mass_fixup(const AttnGeom& a, const AttnSplit& sp, const RowStats& rs, const PageWork& pw,
                              float* fpart, int* arrive, int parts, float* mass, int chunk, hipStream_t s);
 
@@ -192,6 +191,7 @@ struct MeasureBatch {
   int page_groups;        // row groups of the page workgroups (with nw = 4)
   int max_split_groups, max_rb_heads, max_heads, max_combine, max_page_blocks;
   int fix_blocks;         // fix-up blocks per problem
+  bool mass_fixup;        // the fix-up runs in the token mass's launch
   int mass_ppw;           // token mass: 1 or 2 (fast form), 0: general form
   int mass_nz, max_mass_x;
 };

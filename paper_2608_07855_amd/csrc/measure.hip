@@ -1503,18 +1503,6 @@ __device__ __forceinline__ void token_mass_body(const AttnGeom& a, const RowStat
   const int n_pairs = a.group * nrb;
   const int p0 = bz * NP;
   const int np_blk = min(NP, n_pairs - p0);
-  // smallest window position (every head has the same window rows)
-  if (tid == 0) sMin = INT_MAX;
-  __syncthreads();
-  {
-    int q = INT_MAX;
-    for (int p = tid; p < a.W; p += NT) q = min(q, a.qpos[p]);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) q = min(q, __shfl_xor(q, off, 64));
-    if (lane == 0) atomicMin(&sMin, q);
-  }
-  __syncthreads();
-  const int minq = sMin;
 
   bf16x8 qa[PPW][KS];
   float l2[PPW][16];
@@ -1560,6 +1548,22 @@ __device__ __forceinline__ void token_mass_body(const AttnGeom& a, const RowStat
     st.pok = tid < nv;
     st.pr = ldg_i32(a.pos + (st.pok ? t0 + tid : 0));
   };
+  // the rows' state and the first tiles are on their way before anything waits
+  issue(sa, 0);
+  issue(sb, 1);
+  // smallest window position (every head has the same window rows)
+  if (tid == 0) sMin = INT_MAX;
+  __syncthreads();
+  {
+    int q = INT_MAX;
+    for (int p = tid; p < a.W; p += NT) q = min(q, a.qpos[p]);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) q = min(q, __shfl_xor(q, off, 64));
+    if (lane == 0) atomicMin(&sMin, q);
+  }
+  __syncthreads();
+  const int minq = sMin;
+
   auto commit = [&](const KStage& st, int b) {
 #pragma unroll
     for (int i = 0; i < KPT; ++i) {
@@ -1575,24 +1579,30 @@ __device__ __forceinline__ void token_mass_body(const AttnGeom& a, const RowStat
   };
   auto compute = [&](int b, int it) {
     const bool full = sFull[b];
+    if (!pon[0]) return;
 #pragma unroll
-    for (int j = 0; j < PPW; ++j) {
-      if (!pon[j]) continue;
+    for (int tb = 0; tb < 2; ++tb) {
+      // a key fragment read from LDS once serves every pair of the wave
+      f32x16 acc[PPW];
 #pragma unroll
-      for (int tb = 0; tb < 2; ++tb) {
-        f32x16 acc = zero16();
+      for (int j = 0; j < PPW; ++j) acc[j] = zero16();
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          acc = mfma_bf16(qa[j][ks], load_bf16x8(&sK[b][(32 * tb + col) * KP + 16 * ks + 8 * half]), acc);
+      for (int ks = 0; ks < KS; ++ks) {
+        const bf16x8 kf = load_bf16x8(&sK[b][(32 * tb + col) * KP + 16 * ks + 8 * half]);
+#pragma unroll
+        for (int j = 0; j < PPW; ++j) acc[j] = mfma_bf16(qa[j][ks], kf, acc[j]);
+      }
+#pragma unroll
+      for (int j = 0; j < PPW; ++j) {
         float msum = 0.f;
         if (full) {
 #pragma unroll
-          for (int r = 0; r < 16; ++r) msum += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[r], a.sl2, -l2[j][r]));
+          for (int r = 0; r < 16; ++r) msum += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[j][r], a.sl2, -l2[j][r]));
         } else {
           const int pt = sP[b][32 * tb + col];
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[r], a.sl2, -l2[j][r]));
+            const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[j][r], a.sl2, -l2[j][r]));
             msum += pt <= qp[j][r] ? e : 0.f;
           }
         }
@@ -1617,8 +1627,6 @@ __device__ __forceinline__ void token_mass_body(const AttnGeom& a, const RowStat
       atomic_max_nonneg(&mass[t0 + tid], best);
     }
   };
-  issue(sa, 0);
-  issue(sb, 1);
   commit(sa, 0);
   __syncthreads();
   for (int it = 0; it < n_tiles; it += 2) {
@@ -1637,7 +1645,8 @@ __device__ __forceinline__ void token_mass_body(const AttnGeom& a, const RowStat
 }
 
 template <int D, int PPW, bool PG>
-__global__ __launch_bounds__(kNW * 64) void token_mass_fast(AttnGeom a, RowStats rs, float* mass, int chunk) {
+__global__ __launch_bounds__(kNW * 64, PPW == 1 ? 4 : 2) void token_mass_fast(AttnGeom a, RowStats rs, float* mass,
+                                                                                int chunk) {
   token_mass_body<D, PPW, PG>(a, rs, mass, chunk, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
@@ -1645,7 +1654,8 @@ __global__ __launch_bounds__(kNW * 64) void token_mass_fast(AttnGeom a, RowStats
 // pass runs both after the page kernel): blocks [0, nfix) are fix-up
 // blocks, the rest the token-mass grid (mx x my x mz) in x-fastest order.
 // The fix-up is a short chain of dependent latencies; here it runs in the
-// shadow of the token mass instead of taking a launch of its own.
+// shadow of the token mass instead of taking a launch of its own (see
+// mass_fixup_applies).
 template <int D, int PPW, bool PG>
 __global__ __launch_bounds__(kNW * 64) void mass_fixup_kernel(AttnGeom a, AttnSplit sp, RowStats rs, PageWork pw,
                                                               float* fpart, int* arrive, int parts, float* mass,
@@ -1800,17 +1810,12 @@ hipError_t launch_measure_batch(const MeasureProb* dev, const MeasureBatch& b, i
       else hipLaunchKernelGGL((page_fixup_batch<64, false>), grid, block, 0, s, dev, kFixParts);
     }
   } else if (b.mass_ppw > 0) {
-    const int nfix = b.any_pages ? b.fix_blocks : 0;
+    const int nfix = b.mass_fixup ? b.fix_blocks : 0;
     dim3 grid(nfix + b.max_mass_x * b.max_heads * b.mass_nz, 1, b.n), block(kNW * 64);
 #define CKV_K(DD, PP, QQ) \
   hipLaunchKernelGGL((mass_fixup_batch<DD, QQ, PP>), grid, block, 0, s, dev, kFixParts, nfix, b.max_mass_x, b.mass_nz)
-    if (D == 128) {
-      if (pg) { if (b.mass_ppw == 1) CKV_K(128, true, 1); else CKV_K(128, true, 2); }
-      else { if (b.mass_ppw == 1) CKV_K(128, false, 1); else CKV_K(128, false, 2); }
-    } else {
-      if (pg) { if (b.mass_ppw == 1) CKV_K(64, true, 1); else CKV_K(64, true, 2); }
-      else { if (b.mass_ppw == 1) CKV_K(64, false, 1); else CKV_K(64, false, 2); }
-    }
+    if (b.mass_ppw == 1) CKV_DP(CKV_K, 1);
+    else CKV_DP(CKV_K, 2);
 #undef CKV_K
   } else {
     dim3 grid(b.max_mass_x, b.max_heads, b.n), block(kNW * 64);
@@ -1843,17 +1848,28 @@ hipError_t launch_page_fixup(const AttnGeom& a, const AttnSplit& sp, const RowSt
 }
 
 // (query head, 32-row block) pairs per wave of the fast token-mass form, 0
-// for shapes whose heads do not fill whole workgroups
+// for shapes whose heads do not fill whole workgroups.  One pair a wave keeps
+// the kernel within 128 registers, four waves a SIMD, and more pairs take
+// slices of 8: at 131072 tokens and 32 pairs 393 us with two pairs a wave and
+// two waves a SIMD, 330 with slices (their keys come from the L2).  Only
+// heads of 16 row blocks take two.
 int mass_pairs_per_wave(const AttnGeom& a) {
-  const int nrb = (a.W + 31) / 32, n_pairs = a.group * nrb;
-  const int ppw = n_pairs <= kNW ? 1 : 2;
-  return (kNW * ppw) % nrb == 0 ? ppw : 0;
+  const int nrb = (a.W + 31) / 32;
+  return kNW % nrb == 0 ? 1 : (2 * kNW) % nrb == 0 ? 2 : 0;
 }
 int mass_slices(const AttnGeom& a, int ppw) {
   const int n_pairs = a.group * ((a.W + 31) / 32);
   return (n_pairs + kNW * ppw - 1) / (kNW * ppw);
 }
-bool mass_fixup_applies(const AttnGeom& a) { return mass_pairs_per_wave(a) > 0; }
+// The fix-up joins the token mass's launch where that leaves compute units
+// idle: at 2048 tokens and 4 heads the two take 9 us together and 7 + 8
+// apart.  Where the token mass fills the device its workgroups wait for the
+// fix-up's and slow them down: at 32768 tokens and 32 heads (512 workgroups)
+// 55-64 us together, 31 + 15 apart.
+bool mass_fixup_applies(const AttnGeom& a, int chunk) {
+  const int ppw = mass_pairs_per_wave(a);
+  return ppw > 0 && (a.S + chunk - 1) / chunk * a.Hkv * mass_slices(a, ppw) <= 256;
+}
 
 hipError_t launch_mass_fixup(const AttnGeom& a, const AttnSplit& sp, const RowStats& rs, const PageWork& pw,
                              float* fpart, int* arrive, int parts, float* mass, int chunk, hipStream_t s) {
