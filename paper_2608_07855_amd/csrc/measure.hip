@@ -358,20 +358,6 @@ __device__ __forceinline__ void window_attention_body(const AttnGeom& a, const A
   const uint16_t* kh = a.k + (int64_t)g * a.kv_head_stride;
   const uint16_t* vh = a.v + (int64_t)g * a.kv_head_stride;
 
-  const RowInfo ri = row_info(a, g, rblk * kRowsWG + wave * 32 + col);
-  const bool wave_on = __ballot(ri.ok) != 0ull;
-  const int minq = block_min_qpos(ri, &sMin);
-  bf16x8 qf[KS];
-  load_q<D>(a, g, ri, half, qf);
-
-  f32x16 oacc[DB];
-#pragma unroll
-  for (int db = 0; db < DB; ++db) oacc[db] = zero16();
-  float mref = -INFINITY, l = 0.f;
-  int cnt = 0;
-  int mt = -1;          // start of the tile where mref last grew
-  float mp = -INFINITY;  // mref before that tile
-
   const int n_tiles = t_end > t_begin ? (t_end - t_begin + kTile - 1) / kTile : 0;
   // Loads run two tiles ahead of the math: stager A holds even tiles, B odd
   // ones; a tile past the end is an empty segment (its loads read token 0).
@@ -381,6 +367,24 @@ __device__ __forceinline__ void window_attention_body(const AttnGeom& a, const A
     st.issue(kh, vh, (uint32_t)a.kv_tok_stride, a.slot, a.pool_last, a.pos, t0, min(32, n), t0 + 32,
              max(0, n - 32), tid, a.S, a.dbg);
   };
+  // the first tiles' loads leave before anything waits for a load
+  const RowInfo ri = row_info(a, g, rblk * kRowsWG + wave * 32 + col);
+  bf16x8 qf[KS];
+  load_q<D>(a, g, ri, half, qf);
+  St stA, stB;
+  issue(stA, 0);
+  if (NBUF == 2) issue(stB, 1);
+  const bool wave_on = __ballot(ri.ok) != 0ull;
+  const int minq = block_min_qpos(ri, &sMin);
+
+  f32x16 oacc[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db) oacc[db] = zero16();
+  float mref = -INFINITY, l = 0.f;
+  int cnt = 0;
+  int mt = -1;          // start of the tile where mref last grew
+  float mp = -INFINITY;  // mref before that tile
+
   auto compute = [&](int b, int it) {
     if (wave_on) {
       f32x16 s[2];
@@ -475,8 +479,6 @@ __device__ __forceinline__ void window_attention_body(const AttnGeom& a, const A
     cnt = 0;
     mt = -1;
   };
-  St stA;
-  issue(stA, 0);
   if constexpr (NBUF == 1) {
     for (int it = 0; it < n_tiles; ++it) {
       stA.commit(sK[0], sV[0], sP[0], sFull[0], minq, tid);
@@ -487,8 +489,6 @@ __device__ __forceinline__ void window_attention_body(const AttnGeom& a, const A
       __syncthreads();
     }
   } else {
-    St stB;
-    issue(stB, 1);
     if (n_tiles > 0) stA.commit(sK[0], sV[0], sP[0], sFull[0], minq, tid);
     __syncthreads();
     for (int it = 0; it < n_tiles; it += 2) {
@@ -716,6 +716,25 @@ __device__ __forceinline__ void page_body(const AttnGeom& a, const PageWork& pw,
   const RowInfo ri = row_info(a, g, rblk * kRowsWG + (wave % RW) * 32 + col);
   const bool wave_on = __ballot(ri.ok) != 0ull;
   const int minq = block_min_qpos(ri, &sMin);    // its barriers also publish the page spans
+  auto pstart = [&](int item) { return sItStart[item - i_begin]; };
+  auto plen = [&](int item) { return sItLen[item - i_begin] & 0xff; };
+  // pages in the tile that starts at item `it`: two short pages share a tile
+  auto tile_items = [&](int it) {
+    return (it + 1 < i_end && plen(it) <= 32 && plen(it + 1) <= 32) ? 2 : 1;
+  };
+  // the segments of that tile
+  auto tile_seg = [&](int it) {
+    const int s0 = pstart(it), l0 = plen(it);
+    return tile_items(it) == 2 ? make_int4(s0, l0, pstart(it + 1), plen(it + 1))
+                               : make_int4(s0, min(l0, 32), s0 + 32, max(0, l0 - 32));
+  };
+  auto issue_seg = [&](St& st, const int4& sg) {
+    st.issue(kh, vh, (uint32_t)a.kv_tok_stride, a.slot, a.pool_last, a.pos, sg.x, sg.y, sg.z, sg.w, tid, a.S,
+             a.dbg);
+  };
+  // the first tile's loads leave before the rows' state is read
+  St st;
+  issue_seg(st, tile_seg(i_begin));
   bf16x8 qf[KS];
   load_q<D>(a, g, ri, half, qf);
   // o_p in accumulator layout: register r of block db holds width 32db + 8(r/4) + 4h + r%4
@@ -751,21 +770,13 @@ __device__ __forceinline__ void page_body(const AttnGeom& a, const PageWork& pw,
     if (tid == 0) sFixN = 0;
   }
 
-  auto pstart = [&](int item) { return sItStart[item - i_begin]; };
-  auto plen = [&](int item) { return sItLen[item - i_begin] & 0xff; };
-  // pages in the tile that starts at item `it`: two short pages share a tile
-  auto tile_items = [&](int it) {
-    return (it + 1 < i_end && plen(it) <= 32 && plen(it + 1) <= 32) ? 2 : 1;
-  };
   // the block's tile sequence, built once (thread 0) into LDS
   if (tid == 0) {
     int k = 0;
     for (int it = i_begin; it < i_end; ++k) {
       const int m = tile_items(it);
-      const int s0 = pstart(it), l0 = plen(it);
       sTileIt[k] = it;
-      sTileSeg[k] = m == 2 ? make_int4(s0, l0, pstart(it + 1), plen(it + 1))
-                           : make_int4(s0, min(l0, 32), s0 + 32, max(0, l0 - 32));
+      sTileSeg[k] = tile_seg(it);
       it += m;
     }
     sTileIt[k] = i_end;
@@ -776,9 +787,7 @@ __device__ __forceinline__ void page_body(const AttnGeom& a, const PageWork& pw,
   // The next tile's loads are issued before the current tile's math; a tile
   // index past the end is an empty segment (its loads read token 0).
   auto issue_tile = [&](St& st, int k) {
-    const int4 sg = k < n_tiles ? sTileSeg[k] : make_int4(0, 0, 0, 0);
-    st.issue(kh, vh, (uint32_t)a.kv_tok_stride, a.slot, a.pool_last, a.pos, sg.x, sg.y, sg.z, sg.w, tid, a.S,
-             a.dbg);
+    issue_seg(st, k < n_tiles ? sTileSeg[k] : make_int4(0, 0, 0, 0));
   };
   // A row sees at least nvis tokens; a page (at most kMaxPage tokens) can
   // hold all of them only if nvis <= kMaxPage, so most waves skip the count.
@@ -947,8 +956,6 @@ __device__ __forceinline__ void page_body(const AttnGeom& a, const PageWork& pw,
     if (m == 2 && (SG == 1 || wave >= RW)) page(b, it + 1, m, 1);
   };
 
-  St st;
-  issue_tile(st, 0);
   if constexpr (NBUF == 2) {
     st.commit(sK[0], sV[0], sP[0], sFull[0], minq, tid);
     __syncthreads();
@@ -1746,7 +1753,7 @@ hipError_t launch_page_kernel(const AttnGeom& a, const PageWork& pw, const RowSt
   dim3 grid(nblk, (a.rows + 32 * kNW - 1) / (32 * kNW), a.Hkv), block(kNW * 64);
   const bool two = max_len > 32, pg = a.slot != nullptr;
   // the residual pass is bound by its stores and takes one form
-  const bool sg2 = mode == 0 && page_row_groups(kNW, a.rows) == 2;
+  const bool sg2 = mode == 0 && pw.items_per_block > 1 && page_row_groups(kNW, a.rows) == 2;
 #define CKV_PAGE_LAUNCH(DD, MM, SS)                                                                   \
   do {                                                                                                \
     if (pg) {                                                                                         \
