@@ -1057,27 +1057,30 @@ __device__ __forceinline__ int fix_parts(int parts, int item_budget, int n, int 
   return max(parts, min(grow, cap * parts / m));
 }
 
-// ratio of listed pair e from its parts' sums (one wave)
-template <int D>
-__device__ void fixup_ratio(const AttnGeom& a, const RowStats& rs, const PageWork& pw, const float* fpart, int e,
-                            int parts, int lane) {
-  const int4 ent = reinterpret_cast<const int4*>(pw.fix_list)[e];
-  const int page = (int)CKV_IDX(ent.x, pw.n_pages, a.dbg, 8), rg = (int)CKV_IDX(ent.y, a.Hq * a.W, a.dbg, 7);
-  const int h = rg / a.W;
-  const float* fp = fpart + (size_t)e * parts * (D + 1);
+// adds the sums of parts [p0, p1) of a listed pair in order (one wave: the
+// lane's widths lane + 64 j, the weight sum in every lane)
+template <int D, int U>
+__device__ __forceinline__ void fixup_add_parts(const float* fp, int p0, int p1, int lane, float (&num)[D / 64],
+                                                float& den) {
   auto ld = [](const float* p) {
     return __uint_as_float(__hip_atomic_load(reinterpret_cast<const unsigned*>(p), __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT));
   };
-  float num[D / 64], den = 0.f;
-#pragma unroll
-  for (int j = 0; j < D / 64; ++j) num[j] = 0.f;
-#pragma unroll 8
-  for (int part = 0; part < parts; ++part) {
+#pragma unroll U
+  for (int part = p0; part < p1; ++part) {
 #pragma unroll
     for (int j = 0; j < D / 64; ++j) num[j] += ld(fp + part * (D + 1) + lane + 64 * j);
     den += ld(fp + part * (D + 1) + D);
   }
+}
+
+// ratio of listed pair e from the sums over its parts (one wave)
+template <int D>
+__device__ void fixup_ratio(const AttnGeom& a, const RowStats& rs, const PageWork& pw, int e,
+                            const float (&num)[D / 64], float den, int lane) {
+  const int4 ent = reinterpret_cast<const int4*>(pw.fix_list)[e];
+  const int page = (int)CKV_IDX(ent.x, pw.n_pages, a.dbg, 8), rg = (int)CKV_IDX(ent.y, a.Hq * a.W, a.dbg, 7);
+  const int h = rg / a.W;
   float dd = 0.f, oo = 0.f;
 #pragma unroll
   for (int j = 0; j < D / 64; ++j) {
@@ -1339,7 +1342,33 @@ __device__ __forceinline__ void page_fixup_body(const AttnGeom& a, const AttnSpl
     if (tid == 0)
       sLast = __hip_atomic_fetch_add(&arrive[e], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
     __syncthreads();
-    if (sLast && tid < 64) fixup_ratio<D>(a, rs, pw, fpart, e, parts, tid);
+    if (!sLast) continue;
+    // The last part to finish adds them up in order; more than kFixParts are
+    // added by every wave, a run of them each, and the runs in order.
+    const float* fp = fpart + (size_t)e * parts * (D + 1);
+    const int lane = tid & 63, wave = tid >> 6;
+    float num[D / 64], den = 0.f;
+#pragma unroll
+    for (int j = 0; j < D / 64; ++j) num[j] = 0.f;
+    if (parts <= kFixParts) {
+      if (wave == 0) fixup_add_parts<D, kFixParts>(fp, 0, parts, lane, num, den);
+    } else {
+      const int run = (parts + T / 64 - 1) / (T / 64);
+      fixup_add_parts<D, 8>(fp, min(parts, wave * run), min(parts, (wave + 1) * run), lane, num, den);
+#pragma unroll
+      for (int j = 0; j < D / 64; ++j) sacc[wave][lane + 64 * j] = num[j];
+      if (lane == 0) sacc[wave][D] = den;
+      __syncthreads();
+      if (wave == 0) {
+        for (int w = 1; w < T / 64; ++w) {
+#pragma unroll
+          for (int j = 0; j < D / 64; ++j) num[j] += sacc[w][lane + 64 * j];
+          den += sacc[w][D];
+        }
+      }
+    }
+    if (wave == 0) fixup_ratio<D>(a, rs, pw, e, num, den, lane);
+    __syncthreads();   // the next item writes sacc and sLast
   }
 }
 
