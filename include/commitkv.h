@@ -341,9 +341,15 @@ int ckv_measure_page_effects_noalloc(ckv_ctx* ctx, const ckv_kv_view* kv,
  * reads kv[i], win[i], pages[i] (arrays of n views) and writes R[i],
  * R_head[i], o[i], lse[i], token_mass[i] (host arrays of n device pointers;
  * an optional array may be NULL as a whole or hold NULL entries).  Every
- * problem is validated before anything is enqueued; the problems then run
- * in order on the context's stream, reusing one workspace.  A workspace or
- * HIP failure part-way returns the error with the earlier problems enqueued.
+ * problem is validated before anything is enqueued.  The results are those
+ * of single calls in this order: consecutive problems of like shape run
+ * beside each other, one launch per kernel, and a problem that writes
+ * memory which another one of such a run reads or writes (one scratch `o`
+ * for every layer, say) starts the next run.  A run holds the workspace of
+ * all its problems, at most 384 MiB together (and at most the limit of
+ * ckv_set_workspace_limit); problems whose workspace does not fit run one by
+ * one.  A workspace or HIP failure part-way returns the error; the outputs of
+ * the run it names are not valid, those of the earlier problems are enqueued.
  */
 int ckv_measure_page_effects_batch(ckv_ctx* ctx, int32_t n,
                                    const ckv_kv_view* kv,

@@ -6,6 +6,7 @@
 #include "commitkv.h"
 #include "ckv_host.h"
 #include "ckv_kernels.h"
+#include "ckv_plan.h"
 #include "ckv_trace.h"
 
 #include <hip/hip_runtime.h>
@@ -796,6 +797,30 @@ bool same_kernels(const BatchItem& x, const BatchItem& y) {
          mass_fixup_applies(x.a, mass_chunk(x.a)) == mass_fixup_applies(y.a, mass_chunk(y.a)) && (ppw == 0 || mass_slices(x.a, ppw) == mass_slices(y.a, ppw));
 }
 
+// The device memory that a problem reads (K, V, positions, slots, queries and
+// their positions) and writes (its outputs).
+struct ItemMemory {
+  ckv::ByteRange reads[6], writes[5];
+  explicit ItemMemory(const BatchItem& x) {
+    const AttnGeom& a = x.a;
+    const int64_t rows = a.slot ? (int64_t)a.pool_last + 1 : a.S;
+    const int64_t kv = 2 * ((a.Hkv - 1) * a.kv_head_stride + (rows - 1) * a.kv_tok_stride + a.D);
+    const int64_t qh = (a.Hq - 1) * a.q_head_stride;   // the one stride that may be negative
+    const int64_t total_rows = (int64_t)a.Hq * a.W, n = x.pages->n_pages, f = sizeof(float);
+    reads[0] = ckv::byte_range(a.k, kv);
+    reads[1] = ckv::byte_range(a.v, kv);
+    reads[2] = ckv::byte_range(a.pos, a.S * f);
+    reads[3] = ckv::byte_range(a.slot, a.S * f);
+    reads[4] = ckv::byte_range(a.q + std::min<int64_t>(qh, 0), 2 * (std::abs(qh) + (a.W - 1) * a.q_row_stride + a.D));
+    reads[5] = ckv::byte_range(a.qpos, a.W * f);
+    writes[0] = ckv::byte_range(x.R, n * f);
+    writes[1] = ckv::byte_range(x.R_head, n * a.Hq * f);
+    writes[2] = ckv::byte_range(x.o, total_rows * a.D * f);
+    writes[3] = ckv::byte_range(x.lse, total_rows * f);
+    writes[4] = ckv::byte_range(x.mass, a.S * f);
+  }
+};
+
 // Working memory of the problems one launch serves together, at most.  At
 // 4224 tokens and 40 window rows per KV head (7 MB a problem) that is the
 // whole of a 40-layer commit; a 65536-token layer (45 MB) fills the device by
@@ -977,8 +1002,10 @@ extern "C" int ckv_measure_page_effects_batch(ckv_ctx* c, int32_t n, const ckv_k
   if (n == 0) return CKV_OK;
   DeviceGuard g(c->device);
   if (!g.ok) return fail(c, CKV_ERR_HIP, "cannot select device %d", c->device);
-  // runs of problems that share their kernels and whose workspace stays
-  // bounded go out together, the rest one by one
+  // runs of problems that share their kernels, whose workspace stays bounded
+  // and of which none writes what another one reads or writes go out
+  // together, the rest one by one: the results are those of single calls in
+  // order (40 layers: 5-10 us of host work)
   std::vector<BatchItem> items(n);
   for (int i = 0; i < n; ++i)
     items[i] = BatchItem{make_geom(c, &kv[i], &win[i]), &pages[i], max_page_len(&pages[i]), R[i],
@@ -996,7 +1023,11 @@ extern "C" int ckv_measure_page_effects_batch(ckv_ctx* c, int32_t n, const ckv_k
   const size_t cap = c->ws_limit ? std::min(c->ws_limit, kBatchBytes) : kBatchBytes;
   for (int i = 0; i < n;) {
     int m = 0;
+    ckv::RunMemory mem;
     for (size_t total = 0; i + m < n && m < kBatchMax && same_kernels(items[i], items[i + m]); ++m) {
+      const ItemMemory im(items[i + m]);
+      if (m > 0 && !mem.independent(im.reads, im.writes)) break;
+      mem.add(im.reads, im.writes);
       Plan plan;
       MeasureBufs b;
       int32_t* table = nullptr;

@@ -1,0 +1,76 @@
+// Host-side rules that decide how calls are launched, free of HIP so that they
+// can be compiled and checked on their own.
+#pragma once
+
+#include <algorithm>
+#include <cstdint>
+#include <vector>
+
+namespace ckv {
+
+// Bytes [lo, hi) of device memory; empty when lo >= hi.
+struct ByteRange {
+  uintptr_t lo = 0, hi = 0;
+  bool empty() const { return lo >= hi; }
+};
+
+inline ByteRange byte_range(const void* p, int64_t bytes) {
+  const uintptr_t a = reinterpret_cast<uintptr_t>(p);
+  return p && bytes > 0 ? ByteRange{a, a + (uintptr_t)bytes} : ByteRange{};
+}
+
+// A union of ranges, kept disjoint and ascending (ranges that touch are joined,
+// so the layers of one allocation stay one range).
+class RangeSet {
+ public:
+  bool hits(const ByteRange& x) const {
+    if (x.empty()) return false;
+    const auto it = std::upper_bound(v_.begin(), v_.end(), x.lo,
+                                     [](uintptr_t a, const ByteRange& r) { return a < r.hi; });
+    return it != v_.end() && it->lo < x.hi;
+  }
+  void add(ByteRange x) {
+    if (x.empty()) return;
+    auto b = std::lower_bound(v_.begin(), v_.end(), x.lo,
+                              [](const ByteRange& r, uintptr_t a) { return r.hi < a; });
+    auto e = b;
+    for (; e != v_.end() && e->lo <= x.hi; ++e) {
+      x.lo = std::min(x.lo, e->lo);
+      x.hi = std::max(x.hi, e->hi);
+    }
+    if (b == e) {
+      v_.insert(b, x);
+    } else {
+      *b = x;
+      v_.erase(b + 1, e);
+    }
+  }
+  size_t size() const { return v_.size(); }
+
+ private:
+  std::vector<ByteRange> v_;
+};
+
+// The problems of one launch run beside each other, so they may share what
+// they read but not what any of them writes.
+class RunMemory {
+ public:
+  template <int NR, int NW>
+  bool independent(const ByteRange (&reads)[NR], const ByteRange (&writes)[NW]) const {
+    for (const ByteRange& w : writes)
+      if (w_.hits(w) || r_.hits(w)) return false;
+    for (const ByteRange& r : reads)
+      if (w_.hits(r)) return false;
+    return true;
+  }
+  template <int NR, int NW>
+  void add(const ByteRange (&reads)[NR], const ByteRange (&writes)[NW]) {
+    for (const ByteRange& r : reads) r_.add(r);
+    for (const ByteRange& w : writes) w_.add(w);
+  }
+
+ private:
+  RangeSet r_, w_;
+};
+
+}  // namespace ckv

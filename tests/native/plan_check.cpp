@@ -1,0 +1,76 @@
+// Checks of the launch rules in csrc/ckv_plan.h against brute force (host only).
+#include "ckv_plan.h"
+
+#include <cstdio>
+#include <cstdlib>
+#include <random>
+
+using namespace ckv;
+
+#define CHECK(x)                                                  \
+  do {                                                            \
+    if (!(x)) {                                                   \
+      std::printf("%s:%d: %s\n", __FILE__, __LINE__, #x);         \
+      std::exit(1);                                               \
+    }                                                             \
+  } while (0)
+
+static ByteRange range(int lo, int hi) { return ByteRange{(uintptr_t)lo, (uintptr_t)hi}; }
+
+// RangeSet against a bitmap: empty, touching, nested and joining ranges
+static void range_set() {
+  std::mt19937 rng(1);
+  for (int trial = 0; trial < 2000; ++trial) {
+    RangeSet s;
+    std::vector<bool> bit(64, false);
+    for (int k = 0; k < 12; ++k) {
+      const int a = 1 + rng() % 60, b = 1 + rng() % 60;   // empty when a >= b
+      bool want = false;
+      for (int i = a; i < b; ++i) want = want || bit[i];
+      CHECK(s.hits(range(a, b)) == want);
+      s.add(range(a, b));
+      for (int i = a; i < b; ++i) bit[i] = true;
+      size_t runs = 0;
+      for (int i = 1; i < 64; ++i) runs += bit[i] && !bit[i - 1];
+      CHECK(s.size() == runs);
+    }
+  }
+  CHECK(byte_range(nullptr, 8).empty() && byte_range(&rng, 0).empty());
+}
+
+// A run's members against every pair of them
+static void run_memory() {
+  std::mt19937 rng(2);
+  for (int trial = 0; trial < 5000; ++trial) {
+    struct Problem { ByteRange r[2], w[2]; };
+    std::vector<Problem> run;
+    RunMemory mem;
+    auto overlap = [](const ByteRange& x, const ByteRange& y) {
+      return !x.empty() && !y.empty() && x.lo < y.hi && y.lo < x.hi;
+    };
+    for (int k = 0; k < 6; ++k) {
+      Problem p;
+      for (ByteRange* x : {p.r, p.w})
+        for (int i = 0; i < 2; ++i) {
+          const int lo = 1 + rng() % 200;
+          x[i] = range(lo, lo + rng() % 9);
+        }
+      bool ok = true;
+      for (const Problem& q : run)
+        for (int i = 0; i < 2; ++i)
+          for (int j = 0; j < 2; ++j)
+            ok = ok && !overlap(p.w[i], q.w[j]) && !overlap(p.w[i], q.r[j]) && !overlap(p.r[i], q.w[j]);
+      CHECK(mem.independent(p.r, p.w) == ok);
+      if (!ok) continue;
+      mem.add(p.r, p.w);
+      run.push_back(p);
+    }
+  }
+}
+
+int main() {
+  range_set();
+  run_memory();
+  std::printf("plan checks passed\n");
+  return 0;
+}

@@ -10,6 +10,8 @@ blocks; pages of at most 32 tokens and longer; contiguous and paged caches;
 the token mass in its fast and general forms.  Twelve problems of 32 splits
 and 8 KV heads give a workgroup several splits.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -93,3 +95,31 @@ def test_several_splits_per_workgroup_and_workspace_limit(ckv):
         assert ctx.workspace_bytes() <= limit
         _same(got, ref, f"limit {limit}")
         ctx.close()
+
+
+@pytest.mark.parametrize("shared", ["o", "lse", "R", "R_head", "token_mass"])
+def test_problems_that_share_an_output(ckv, shared):
+    """One buffer for the same output of every problem: the other outputs are
+    those of single calls (R comes from the problem's own o), and the buffer
+    holds the last problem's."""
+    P, ctx = ckv
+    print(f"[batch] shared {shared}", flush=True)
+    hq, d, W = 8, 64, 8
+    pr = [_problem(P, hq, 2, d, S, W, 16, False, seed=50 + i) for i, S in enumerate((900, 700, 820, 641))]
+    ref = [P.ckv_measure_page_effects(ctx, *p[:3], want=WANT) for p in pr]
+    size = lambda key, p: {"R": p[2].n, "R_head": p[2].n * hq, "o": hq * W * d, "lse": hq * W,
+                           "token_mass": p[0].n_tokens}[key]
+    outs = {key: [torch.full((size(key, p),), -3.0, device="cuda") for p in pr] for key in WANT}
+    outs[shared] = [torch.full((max(size(shared, p) for p in pr),), -3.0, device="cuda")] * len(pr)
+    n = len(pr)
+    arrs = [(ctypes.c_void_p * n)(*[t.data_ptr() for t in outs[key]]) for key in WANT]
+    ctx.check(P.lib().ckv_measure_page_effects_batch(
+        ctx.handle, n, (type(pr[0][0]) * n)(*[p[0] for p in pr]), (type(pr[0][1]) * n)(*[p[1] for p in pr]),
+        (type(pr[0][2].view()) * n)(*[p[2].view() for p in pr]), *arrs))
+    torch.cuda.synchronize()
+    for i, (p, s) in enumerate(zip(pr, ref)):
+        for key in WANT:
+            if key == shared and i < n - 1:
+                continue
+            got = outs[key][i][:size(key, p)]
+            assert torch.equal(got.view(torch.int32), s[key].reshape(-1).view(torch.int32)), f"problem {i} {key}"
