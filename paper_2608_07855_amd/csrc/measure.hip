@@ -1405,7 +1405,18 @@ __global__ __launch_bounds__(kFixT) void page_fixup_batch(const MeasureProb* __r
 // fixed block order (deterministic) and the max over heads is taken.
 // ---------------------------------------------------------------------------
 constexpr int kMassMaxRows = 2048;   // window rows per KV head the mass kernel supports
-constexpr int kMassMaxPairs = kMassMaxRows / 32;
+// (query head, 32-row block) pairs of the general form at most: every head
+// rounds its rows up to whole blocks, so there are more than kMassMaxRows / 32
+// (31 heads of 66 rows: 93)
+constexpr int mass_general_pairs() {
+  int most = 0;
+  for (int w = 1; w <= kMassMaxRows; ++w) {
+    const int nrb = (w + 31) / 32, n = kMassMaxRows / w * nrb;
+    if (2 * kNW % nrb != 0 && n > most) most = n;   // others: the fast form
+  }
+  return most;
+}
+constexpr int kMassMaxPairs = mass_general_pairs();
 
 template <int D, bool PG>
 __device__ __forceinline__ void token_mass_general(const AttnGeom& a, const RowStats& rs, float* mass, int chunk,

@@ -50,7 +50,9 @@ def _attend(k, v, q, pos, qpos):
 
 
 @pytest.mark.parametrize("group,W,d,S", [(1, 8, 64, 65), (5, 8, 128, 700), (8, 32, 128, 1025), (3, 96, 64, 513),
-                                         (5, 64, 128, 900), (3, 128, 64, 1200), (8, 128, 128, 2049), (2, 512, 64, 1100)])
+                                         (5, 64, 128, 900), (3, 128, 64, 1200), (8, 128, 128, 2049), (2, 512, 64, 1100),
+                                         # the general form with more pairs than rows / 32: 72, 93, 70
+                                         (24, 65, 64, 200), (31, 66, 128, 200), (14, 146, 64, 300)])
 def test_token_mass_slices(ckv, group, W, d, S):
     P, ctx = ckv
     print(f"[mass] group={group} W={W} d={d} S={S}", flush=True)
@@ -63,7 +65,8 @@ def test_token_mass_slices(ckv, group, W, d, S):
     alone = P.ckv_measure_page_effects(ctx, kv, win, P.Pages([], []), want=("R", "token_mass"))
     rec = P.ckv_measure_recorded(ctx, kv, win, pages, o.float().contiguous(), lse.float().contiguous(),
                                  want=("R", "token_mass"))
-    for got in (fused, alone, rec):
+    two = P.ckv_measure_page_effects_batch(ctx, [kv] * 2, [win] * 2, [pages] * 2, want=("R", "token_mass"))
+    for got in (fused, alone, rec, *two):
         torch.testing.assert_close(got["token_mass"].double(), want, rtol=1e-3, atol=1e-9)
 
 
