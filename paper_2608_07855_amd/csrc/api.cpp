@@ -1246,7 +1246,7 @@ extern "C" int ckv_joint_test(ckv_ctx* c, const ckv_kv_view* kv, const ckv_windo
   plan.add(&j.acc_t, std::max(pages->n_pages, 1));
   j.fix_cap = 2 * ckv::kJointWindow * total_rows;
   plan.add(&j.fix_list, 2 * (size_t)j.fix_cap);
-  plan.add(&j.fpart, (size_t)ckv::kJointFixItems * (D + 1));
+  plan.add(&j.fpart, (size_t)ckv::joint_fix_items(a.S) * (D + 1));
   const int32_t *dstart = nullptr, *dlen = nullptr;
   if ((rc = page_table(c, pages, &dstart, &dlen))) return rc;
   if ((rc = realize(c, plan))) return rc;

@@ -278,14 +278,13 @@ struct JointArgs {
   int32_t* acc_t;         // [n_pages] the candidate that was accepted with this page (INT_MAX: none)
   int* fix_list;          // [fix_cap] (candidate, row) pairs left to the fix-up
   int fix_cap;            // 2 * window * rows: a round adds at most window * rows
-  float* fpart;           // [kJointFixItems][D + 1] partial sums of the fix-up
+  float* fpart;           // [joint_fix_items(S)][D + 1] partial sums of the fix-up
 };
 constexpr int kJointWindow = 32;        // candidates tested per round
 constexpr int kJointBmaxWords = 256 * 2 * kJointWindow;
 constexpr int kJointGmaxWords = 16 * 2 * kJointWindow;
 constexpr int kJointCtrlWords = 20 * 32;
 constexpr float kJointFixA = 0.8f;      // union mass above which a pair is recomputed
-constexpr int kJointFixItems = 30720;   // (pair, segment) items of the fix-up workspace
 int joint_vis_slices(int S);
 bool joint_state_global(int total_rows);
 hipError_t launch_joint(const JointArgs& j, hipStream_t s);

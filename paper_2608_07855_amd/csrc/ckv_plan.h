@@ -73,4 +73,24 @@ class RunMemory {
   RangeSet r_, w_;
 };
 
+// Fix-up of the joint test: a listed (candidate, row) pair is recomputed from
+// segments of its row, one workgroup and one partial sum each, and the pairs
+// whose partial sums fit the workspace go together (at least one).
+constexpr int kJointFixItems = 30720;   // (pair, segment) items aimed at
+constexpr int kFixSegMax = 1024;        // tokens of a segment at most
+
+// tokens per segment for n listed pairs over S tokens: short segments while
+// the items are few
+constexpr int joint_segment(int n, int S) {
+  int seg = 256;
+  while (seg < kFixSegMax && (int64_t)n * ((S - 1) / seg + 1) > 32 * 256) seg *= 2;
+  return seg;
+}
+constexpr int joint_segments(int seg, int S) { return (S - 1) / seg + 1; }
+// pairs recomputed together
+constexpr int joint_pairs(int segments) { return std::max(1, kJointFixItems / segments); }
+// items of the workspace: those, or the segments of one pair where a paged
+// cache is longer than all of them (31.4 million tokens)
+constexpr int joint_fix_items(int S) { return std::max(kJointFixItems, joint_segments(kFixSegMax, S)); }
+
 }  // namespace ckv

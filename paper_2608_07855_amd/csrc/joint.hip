@@ -52,6 +52,7 @@
 // but did not decide are dropped.
 #include "ckv_device.h"
 #include "ckv_kernels.h"
+#include "ckv_plan.h"
 
 #include <algorithm>
 #include <climits>
@@ -74,7 +75,6 @@ constexpr int kJT = 512, kJW = kJT / 64;   // threads and waves of a workgroup
 constexpr int kRowsOwnedMax = 64;      // rows whose state a workgroup keeps in LDS
 constexpr int kJointBlocksMax = 256;   // workgroups at most (one per compute unit)
 constexpr int kCandBatch = 16;         // candidates reduced together
-constexpr int kFixSegMax = 1024;       // tokens of a row per fix-up item at most
 static_assert(kJointWindow == 2 * kCandBatch, "a round's maxima fill one wave: window x 2 guesses");
 
 template <class T>
@@ -552,11 +552,8 @@ __device__ bool joint_flush(const JointArgs& j, JointSync& sy, float* sacc, uint
   if (!joint_sync(j, sy, false, 0, 0, nullptr)) return false;
   const int n = min(ld_agent(&j.ctrl[kFixN]), j.fix_cap);
   if (n == 0) return true;   // the same in every block
-  const int S = j.geo.S;
-  int seg = 256;             // short segments while the items are few
-  while (seg < kFixSegMax && (int64_t)n * ((S + seg - 1) / seg) > 32 * kJointBlocksMax) seg *= 2;
-  const int parts = (S + seg - 1) / seg;
-  const int npc = max(1, kJointFixItems / parts);   // pairs whose partial sums fit the workspace
+  const int seg = joint_segment(n, j.geo.S), parts = joint_segments(seg, j.geo.S);
+  const int npc = joint_pairs(parts);
   for (int e0 = 0; e0 < n; e0 += npc) {
     const int np = min(npc, n - e0);
     if (j.geo.slot) joint_fix_partial<D, true>(j, e0, np, seg, parts, sacc, sMask);

@@ -1,6 +1,7 @@
 // Checks of the launch rules in csrc/ckv_plan.h against brute force (host only).
 #include "ckv_plan.h"
 
+#include <climits>
 #include <cstdio>
 #include <cstdlib>
 #include <random>
@@ -68,9 +69,26 @@ static void run_memory() {
   }
 }
 
+// The joint test's fix-up: the partial sums of the pairs that go together fit
+// the workspace, and the segments cover the row
+static void joint_fixup() {
+  std::vector<int> lengths = {1, 255, 256, 257, 32768, 131072, (1 << 24) - 1, 30720 * 1024 - 1, 30720 * 1024,
+                              30720 * 1024 + 1, 100000000, INT_MAX - 1024};
+  std::mt19937 rng(3);
+  for (int k = 0; k < 2000; ++k) lengths.push_back(1 + rng() % (INT_MAX - 1024));
+  for (int S : lengths)
+    for (int n : {1, 2, 31, 64, 1000, 32768, 2097152}) {
+      const int seg = joint_segment(n, S), parts = joint_segments(seg, S);
+      CHECK(seg >= 256 && seg <= kFixSegMax);
+      CHECK((int64_t)(parts - 1) * seg < S && (int64_t)parts * seg >= S);
+      CHECK((int64_t)std::min(n, joint_pairs(parts)) * parts <= joint_fix_items(S));
+    }
+}
+
 int main() {
   range_set();
   run_memory();
+  joint_fixup();
   std::printf("plan checks passed\n");
   return 0;
 }

@@ -152,3 +152,48 @@ def test_union_not_read(ckv):
     torch.cuda.synchronize()
     np.testing.assert_array_equal(acc2.cpu().numpy()[:6], acc)
     assert int(na.item()) == int(acc.sum())
+
+
+def test_more_segments_than_fixup_items(ckv):
+    """A paged cache of 31.6 million tokens over a pool of 4096 rows: one row of
+    a pair alone has more 1024-token segments (30860) than the fix-up aims at
+    (30720).  Page 0 carries about 0.9 of every row's mass, so both candidates
+    are decided by such pairs.  Reference: float64 over the pool's rows, each
+    weighted by the tokens that map to it."""
+    P, ctx = ckv
+    S, rows, W, d, G = 31_600_000, 4096, 2, 64, 16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(13)
+    k = torch.randn((1, rows, d), generator=g, device="cuda", dtype=torch.bfloat16)
+    v = torch.randn((1, rows, d), generator=g, device="cuda", dtype=torch.bfloat16)
+    q = torch.randn((1, W, d), generator=g, device="cuda", dtype=torch.bfloat16)
+    q[:, :, 0] = 1
+    k[:, :, 0] = 0
+    k[:, :G, 0] = d ** 0.5 * float(np.log(20.0 * (S - G) / G))
+    slot = torch.randint(G, rows, (S,), generator=g, device="cuda", dtype=torch.int32)
+    slot[:G] = torch.arange(G, dtype=torch.int32, device="cuda")
+    pos = torch.arange(S, dtype=torch.int32, device="cuda")
+    kv, win = P.kv_view(k, v, pos, S, slot=slot), P.window_view(q, pos[S - W:].clone())
+    pages = P.Pages([0, 1000], [G, G])
+    print("[joint rounds] 31.6M tokens", flush=True)
+    m = P.ckv_measure_page_effects(ctx, kv, win, pages, want=("R", "o", "lse"))
+    out = P.ckv_joint_test(ctx, kv, win, m["o"], m["lse"], pages, torch.tensor([0, 1], dtype=torch.int32, device="cuda"),
+                           torch.tensor([2], dtype=torch.int32, device="cuda"), 2, 1e30)
+    torch.cuda.synchronize()
+    ctx.sync()
+
+    def output(p, gone):
+        count = torch.bincount(slot[:S - W + p + 1].long(), minlength=rows).double()
+        for s in gone:
+            count -= torch.bincount(slot[s:s + G].long(), minlength=rows).double()
+        x = (k[0].double() @ q[0, p].double()) / d ** 0.5
+        w = count * torch.exp(x - x.max())
+        return (w / w.sum()) @ v[0].double()
+
+    ref = np.zeros(2)
+    for t, gone in enumerate(([0], [0, 1000])):
+        for p in range(W):
+            o = output(p, [])
+            ref[t] = max(ref[t], float((o - output(p, gone)).norm() / o.norm()))
+    assert out["accepted"].cpu().tolist() == [1, 1] and int(out["n_accepted"].item()) == 2
+    assert_scores_close(out["union_R"].cpu().numpy(), ref, "union_R")
