@@ -275,7 +275,7 @@ struct JointArgs {
   const int32_t* plen;
   int n_pages;
   const int32_t* cand;    // [max_cand] page of each candidate
-  int32_t* acc_t;         // [n_pages] the candidate that was accepted with this page (INT_MAX: none)
+  int32_t* acc_t;         // [n_pages] the first candidate accepted with this page (INT_MAX: none)
   int* fix_list;          // [fix_cap] (candidate, row) pairs left to the fix-up
   int fix_cap;            // 2 * window * rows: a round adds at most window * rows
   float* fpart;           // [joint_fix_items(S)][D + 1] partial sums of the fix-up

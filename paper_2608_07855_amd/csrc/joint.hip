@@ -272,6 +272,12 @@ __device__ void joint_reduce(const unsigned* words, int n, unsigned* sRed, int* 
   __syncthreads();
 }
 
+// Page ap was accepted with candidate t.  A page that is listed twice keeps the
+// earlier candidate: it is gone for every candidate after that one.
+__device__ __forceinline__ void mark_accepted(const JointArgs& j, int ap, int t) {
+  __hip_atomic_fetch_min(&j.acc_t[ap], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // The decision of a round from its maxima (the workgroup that arrives last);
 // the payload in thread 0.
 __device__ unsigned joint_decide(const JointArgs& j, int cursor, int n_eff, const unsigned* sRed,
@@ -300,7 +306,7 @@ __device__ unsigned joint_decide(const JointArgs& j, int cursor, int n_eff, cons
   if (mine && c < dec && (chain ? c < n : c == n)) {
     st_agent(&j.accepted[t], (uint8_t)1);
     const int ap = j.cand[t];
-    if (ap >= 0 && ap < j.n_pages) st_agent(&j.acc_t[ap], t);
+    if (ap >= 0 && ap < j.n_pages) mark_accepted(j, ap, t);
   }
   unsigned p = (chain ? kDecChain : 0u) | (unsigned)n << 1 | (extra ? kDecExtra : 0u) |
                (resolve ? kDecResolve : 0u) | (defer ? kDecDefer : 0u);
@@ -687,7 +693,7 @@ __global__ __launch_bounds__(kJT) void joint_rounds(JointArgs j) {
       if (pass && gid == 0) {
         st_agent(&j.accepted[cursor], (uint8_t)1);
         const int ap = j.cand[cursor];
-        if (ap >= 0 && ap < j.n_pages) st_agent(&j.acc_t[ap], cursor);
+        if (ap >= 0 && ap < j.n_pages) mark_accepted(j, ap, cursor);
       }
       cursor += 1;
     } else {

@@ -137,6 +137,23 @@ def test_union_above_the_closed_form(ckv, gate):
     _check(layer, cand, acc, u, tau)
 
 
+@pytest.mark.parametrize("again", [2, 5, 40])
+def test_page_listed_twice(ckv, again):
+    """The heavy page is candidate 0 and candidate `again` (of the same round, or
+    of the next): candidates in between, which are recomputed by definition,
+    miss its tokens all the same."""
+    P, ctx = ckv
+    layer = _layer(4, 2, 64, 1300, 32, 16, seed=14, heavy_first=True)
+    cand = np.insert(np.arange(45), again, 0)
+    ctx.set_policy("no_joint")
+    try:
+        acc, u, tau, _ = _run(P, ctx, layer, cand, 1e30)
+    finally:
+        ctx.set_policy()
+    assert acc.all()
+    _check(layer, cand, acc, u, tau)
+
+
 def test_union_not_read(ckv):
     """union_R NULL: the same decisions."""
     P, ctx = ckv
