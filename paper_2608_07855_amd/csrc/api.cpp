@@ -1231,7 +1231,9 @@ extern "C" int ckv_joint_test(ckv_ctx* c, const ckv_kv_view* kv, const ckv_windo
   plan.add(&resid, (size_t)max_cand * total_rows * D);
   plan.add(&resA, (size_t)max_cand * total_rows);
   plan.add(&resC, (size_t)max_cand * total_rows);
-  if (joint_state_global(total_rows)) {
+  bool state_global = false;
+  CKV_HIP(c, ckv::joint_needs_global_state(D, total_rows, &state_global));
+  if (state_global) {
     plan.add(&j.st_D, (size_t)total_rows * D);
     plan.add(&j.st_A, total_rows);
     plan.add(&j.st_C, total_rows);

@@ -247,7 +247,7 @@ struct JointArgs {
   const int32_t* qpos;    // [W] window positions
   int S;
   int test_cap;           // candidates tested at most (0: none, e.g. no pages)
-  // the rows' state when it does not fit LDS (joint_state_global), else null:
+  // the rows' state when it does not fit LDS (joint_needs_global_state), else null:
   // accumulated residual [rows][D], mass, visible count, ||o_p||, visible
   // tokens [rows] and fix-up bits [rows][2]
   float* st_D;
@@ -286,7 +286,8 @@ constexpr int kJointGmaxWords = 16 * 2 * kJointWindow;
 constexpr int kJointCtrlWords = 20 * 32;
 constexpr float kJointFixA = 0.8f;      // union mass above which a pair is recomputed
 int joint_vis_slices(int S);
-bool joint_state_global(int total_rows);
+// whether the call has to give the rows' state room in global memory (JointArgs::st_D ..)
+hipError_t joint_needs_global_state(int D, int total_rows, bool* global);
 hipError_t launch_joint(const JointArgs& j, hipStream_t s);
 
 // checkpoint: protection, selection, compaction (Eq. (12)-(13), Eq. (4))

@@ -73,6 +73,22 @@ class RunMemory {
   RangeSet r_, w_;
 };
 
+// Workgroups of the joint test (8 waves each) for so many window rows: about
+// one row per wave, at most as many as the device holds at once and one per
+// compute unit of a whole device.
+constexpr int kJointWaves = 8;
+constexpr int kJointBlocksMax = 256;
+constexpr int kJointRowsLds = 64;       // rows whose state a workgroup keeps in LDS at most
+constexpr int joint_blocks(int rows, int resident) {
+  return std::max(1, std::min({(rows - 1) / kJointWaves + 1, resident, kJointBlocksMax}));
+}
+// Whether the rows' state has to live in global memory: where the workgroups
+// that the device holds of the LDS form would own more rows than fit (above
+// 16384 rows on 256 compute units, above 2048 on a partition of 32).
+constexpr bool joint_state_global(int rows, int resident) {
+  return (rows - 1) / joint_blocks(rows, resident) + 1 > kJointRowsLds;
+}
+
 // Fix-up of the joint test: a listed (candidate, row) pair is recomputed from
 // segments of its row, one workgroup and one partial sum each, and the pairs
 // whose partial sums fit the workspace go together (at least one).

@@ -55,6 +55,7 @@
 #include "ckv_plan.h"
 
 #include <algorithm>
+#include <atomic>
 #include <climits>
 
 namespace ckv {
@@ -71,9 +72,7 @@ static_assert(kGroup0 + 16 * kLine == kJointCtrlWords, "control words");
 constexpr unsigned kDecChain = 1u, kDecExtra = 1u << 7, kDecResolve = 1u << 8, kDecDefer = 1u << 9,
                    kDecFlush = 1u << 10;
 constexpr int kVisSlice = 8192;        // tokens per visible-count item
-constexpr int kJT = 512, kJW = kJT / 64;   // threads and waves of a workgroup
-constexpr int kRowsOwnedMax = 64;      // rows whose state a workgroup keeps in LDS
-constexpr int kJointBlocksMax = 256;   // workgroups at most (one per compute unit)
+constexpr int kJW = kJointWaves, kJT = 64 * kJW;   // waves and threads of a workgroup
 constexpr int kCandBatch = 16;         // candidates reduced together
 static_assert(kJointWindow == 2 * kCandBatch, "a round's maxima fill one wave: window x 2 guesses");
 
@@ -572,10 +571,10 @@ __device__ bool joint_flush(const JointArgs& j, JointSync& sy, float* sacc, uint
   return true;
 }
 
-// LDS: the rows' state is kept in LDS (nr <= kRowsOwnedMax)
+// LDS: the rows' state is kept in LDS (nr <= kJointRowsLds)
 template <int D, bool LDS>
 __global__ __launch_bounds__(kJT) void joint_rounds(JointArgs j) {
-  constexpr int KD = D / 64, NR = LDS ? kRowsOwnedMax : 1;
+  constexpr int KD = D / 64, NR = LDS ? kJointRowsLds : 1;
   __shared__ float sD[LDS ? NR * D : 1];
   __shared__ float sA[NR], sOn[NR];
   __shared__ int sC[NR], sNv[NR];
@@ -713,32 +712,39 @@ JointKernel joint_kernel(int D, bool lds) {
   if (D == 128) return lds ? joint_rounds<128, true> : joint_rounds<128, false>;
   return lds ? joint_rounds<64, true> : joint_rounds<64, false>;
 }
-}  // namespace
 
-// rows a call's workgroups own at most when every workgroup is used; above
-// kRowsOwnedMax the rows' state lives in the caller's workspace
-bool joint_state_global(int total_rows) { return (total_rows + kJointBlocksMax - 1) / kJointBlocksMax > kRowsOwnedMax; }
-
-hipError_t launch_joint(const JointArgs& j, hipStream_t s) {
-  // workgroups of each form that fit on the device at once (queried once per device)
-  static int resident[64][4];
-  int dev = 0;
+// workgroups of one form that fit on the current device at once (queried once
+// per device)
+hipError_t joint_resident(int D, bool lds, int* out) {
+  static std::atomic<int> resident[64][4];
+  int dev = 0, per_cu = 0, cus = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-  const bool lds = !joint_state_global(j.total_rows);
-  const JointKernel kern = joint_kernel(j.D, lds);
-  int& res = resident[dev][(j.D == 128 ? 2 : 0) + (lds ? 1 : 0)];
-  if (res <= 0) {
-    int per_cu = 0, cus = 0;
-    if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kJT, 0)) != hipSuccess) return e;
-    if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-    res = std::max(1, per_cu * cus);
-  }
-  // about one row per wave, at most one workgroup per compute unit
-  const int nb = std::max(1, std::min({(j.total_rows + kJW - 1) / kJW, res, kJointBlocksMax}));
-  if (lds && (j.total_rows + nb - 1) / nb > kRowsOwnedMax) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL(kern, dim3(nb), dim3(kJT), 0, s, j);
+  std::atomic<int>& res = resident[dev][(D == 128 ? 2 : 0) + (lds ? 1 : 0)];
+  if ((*out = res.load(std::memory_order_relaxed)) > 0) return hipSuccess;
+  if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, joint_kernel(D, lds), kJT, 0)) != hipSuccess) return e;
+  if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
+  *out = std::max(1, per_cu * cus);
+  res.store(*out, std::memory_order_relaxed);
+  return hipSuccess;
+}
+}  // namespace
+
+hipError_t joint_needs_global_state(int D, int total_rows, bool* global) {
+  int res = 0;
+  const hipError_t e = joint_resident(D, true, &res);
+  if (e == hipSuccess) *global = joint_state_global(total_rows, res);
+  return e;
+}
+
+hipError_t launch_joint(const JointArgs& j, hipStream_t s) {
+  const bool lds = j.st_D == nullptr;
+  int res = 0;
+  const hipError_t e = joint_resident(j.D, lds, &res);
+  if (e != hipSuccess) return e;
+  if (lds && joint_state_global(j.total_rows, res)) return hipErrorInvalidConfiguration;
+  hipLaunchKernelGGL(joint_kernel(j.D, lds), dim3(joint_blocks(j.total_rows, res)), dim3(kJT), 0, s, j);
   return hipGetLastError();
 }
 

@@ -85,9 +85,26 @@ static void joint_fixup() {
     }
 }
 
+// The joint test's workgroups on devices of any size: every row is owned, no
+// more workgroups than the device holds, and the LDS form only where its rows fit
+static void joint_workgroups() {
+  for (int resident : {1, 2, 16, 32, 38, 64, 128, 255, 256, 304, 512, 4096})
+    for (int rows = 1; rows <= 1 << 20; rows += 1 + rows / 64) {
+      const int nb = joint_blocks(rows, resident), per = (rows + nb - 1) / nb;
+      CHECK(nb >= 1 && nb <= resident && nb <= kJointBlocksMax);
+      CHECK((int64_t)nb * per >= rows);
+      CHECK(joint_state_global(rows, resident) == (per > kJointRowsLds));
+      // a whole device keeps 64 rows a workgroup in LDS
+      if (resident >= kJointBlocksMax) CHECK(joint_state_global(rows, resident) == (rows > 64 * 256));
+    }
+  // 64 heads of 128 rows on 32 compute units
+  CHECK(joint_state_global(64 * 128, 32) && !joint_state_global(32 * 64, 32));
+}
+
 int main() {
   range_set();
   run_memory();
+  joint_workgroups();
   joint_fixup();
   std::printf("plan checks passed\n");
   return 0;
