@@ -345,10 +345,11 @@ int ckv_measure_page_effects_noalloc(ckv_ctx* ctx, const ckv_kv_view* kv,
  * of single calls in this order: consecutive problems of like shape run
  * beside each other, one launch per kernel, and a problem that writes
  * memory which another one of such a run reads or writes (one scratch `o`
- * for every layer, say) starts the next run.  A run holds the workspace of
- * all its problems, at most 384 MiB together (and at most the limit of
- * ckv_set_workspace_limit); problems whose workspace does not fit run one by
- * one.  A workspace or HIP failure part-way returns the error; the outputs of
+ * for every layer, say) starts the next run.  Runs use a workspace of their
+ * own beside the one of the single calls: it holds what all problems of a run
+ * need, at most 384 MiB, counts toward ckv_workspace_bytes and the limit of
+ * ckv_set_workspace_limit, and is freed by ckv_destroy or when a single call
+ * needs its room; problems whose workspace does not fit run one by one.  A workspace or HIP failure part-way returns the error; the outputs of
  * the run it names are not valid, those of the earlier problems are enqueued.
  */
 int ckv_measure_page_effects_batch(ckv_ctx* ctx, int32_t n,

@@ -15,6 +15,7 @@
 #include <climits>
 #include <cmath>
 #include <cstdarg>
+#include <cstdint>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -80,9 +81,12 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 struct ckv_ctx {
   int device = 0;
   hipStream_t stream = nullptr;
-  char* ws = nullptr;
-  size_t ws_cap = 0;
-  size_t ws_limit = 0;
+  // Device memory of the calls, and apart from it that of the runs of a batch:
+  // a run is many times a call, and growing it must not move the memory that
+  // single calls have been recorded with (a captured graph of them).
+  struct Arena { char* p = nullptr; size_t cap = 0; };
+  Arena ws, batch_ws;
+  size_t ws_limit = 0;   // of both together
   std::string err;
   PinnedSlot slots[kPinnedSlots];
   int next_slot = 0;
@@ -192,36 +196,68 @@ int latched_nonfinite(ckv_ctx* c) {
               "on this context (non-finite keys, values or queries, or recorded outputs)");
 }
 
+// gives an arena's memory back (the stream is idle)
+void release(ckv_ctx::Arena& a) {
+  if (a.p) (void)hipFree(a.p);
+  a = ckv_ctx::Arena();
+}
+
+bool allocate(ckv_ctx::Arena& a, size_t bytes) {
+  void* p = nullptr;
+  if (hipMalloc(&p, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  a.p = static_cast<char*>(p);
+  a.cap = bytes;
+  return true;
+}
+
 int ensure_ws(ckv_ctx* c, size_t need) {
-  if (need <= c->ws_cap) return CKV_OK;
+  if (need <= c->ws.cap) return CKV_OK;
   if (c->ws_limit && need > c->ws_limit)
     return fail(c, CKV_ERR_NOMEM, "workspace of %zu bytes exceeds the limit of %zu", need, c->ws_limit);
-  size_t want = std::max(need, c->ws_cap + c->ws_cap / 2);
+  size_t want = std::max(need, c->ws.cap + c->ws.cap / 2);
   if (c->ws_limit) want = std::min(want, c->ws_limit);
   CKV_HIP(c, hipStreamSynchronize(c->stream));   // in-flight work may still use the old arena
-  if (c->ws) {
-    (void)hipFree(c->ws);
-    c->ws = nullptr;
-    c->ws_cap = 0;
+  release(c->ws);
+  // a single call goes before a batch's memory, at the limit and on a full device
+  if (c->ws_limit && c->batch_ws.cap > c->ws_limit - want) release(c->batch_ws);
+  if (allocate(c->ws, want)) return CKV_OK;
+  if (c->batch_ws.p) {
+    release(c->batch_ws);
+    if (allocate(c->ws, want)) return CKV_OK;
   }
-  void* p = nullptr;
-  if (hipMalloc(&p, want) != hipSuccess) {
-    (void)hipGetLastError();
-    return fail(c, CKV_ERR_NOMEM, "hipMalloc of %zu workspace bytes failed", want);
+  return fail(c, CKV_ERR_NOMEM, "hipMalloc of %zu workspace bytes failed", want);
+}
+
+// bytes a run of a batch may hold under the workspace limit, beside `single`
+// bytes for single calls
+size_t batch_limit(const ckv_ctx* c, size_t single) {
+  return c->ws_limit ? c->ws_limit - std::min(c->ws_limit, std::max(c->ws.cap, single)) : SIZE_MAX;
+}
+
+int ensure_batch_ws(ckv_ctx* c, size_t need) {
+  if (need <= c->batch_ws.cap) return CKV_OK;
+  const size_t most = batch_limit(c, 0);
+  if (need > most) return fail(c, CKV_ERR_NOMEM, "workspace of %zu bytes exceeds the limit", need);
+  CKV_HIP(c, hipStreamSynchronize(c->stream));
+  release(c->batch_ws);
+  if (allocate(c->batch_ws, need)) return CKV_OK;
+  return fail(c, CKV_ERR_NOMEM, "hipMalloc of %zu workspace bytes failed", need);
+}
+
+void place(Plan& plan, char* base) {
+  size_t off = 0;
+  for (auto& it : plan.items) {
+    *it.dst = base + off;
+    off += round_up(std::max<size_t>(it.bytes, 1), kAlign);
   }
-  c->ws = static_cast<char*>(p);
-  c->ws_cap = want;
-  return CKV_OK;
 }
 
 int realize(ckv_ctx* c, Plan& plan) {
-  int rc = ensure_ws(c, plan.total);
-  if (rc) return rc;
-  size_t off = 0;
-  for (auto& it : plan.items) {
-    *it.dst = c->ws + off;
-    off += round_up(std::max<size_t>(it.bytes, 1), kAlign);
-  }
+  if (int rc = ensure_ws(c, plan.total)) return rc;
+  place(plan, c->ws.p);
   return CKV_OK;
 }
 
@@ -538,7 +574,8 @@ extern "C" int ckv_destroy(ckv_ctx* c) {
   {
     DeviceGuard g(c->device);   // best effort: the context is freed whatever happens
     (void)hipStreamSynchronize(c->stream);
-    if (c->ws) (void)hipFree(c->ws);
+    release(c->ws);
+    release(c->batch_ws);
     if (c->sel_ctrl) (void)hipFree(c->sel_ctrl);
     if (c->sel_hist) (void)hipFree(c->sel_hist);
     for (auto& e : c->pages)
@@ -596,7 +633,7 @@ extern "C" int ckv_set_workspace_limit(ckv_ctx* c, size_t bytes) {
   return CKV_OK;
 }
 
-extern "C" size_t ckv_workspace_bytes(const ckv_ctx* c) { return c ? c->ws_cap : 0; }
+extern "C" size_t ckv_workspace_bytes(const ckv_ctx* c) { return c ? c->ws.cap + c->batch_ws.cap : 0; }
 
 extern "C" int ckv_set_policy(ckv_ctx* c, uint32_t flags) {
   if (!c) return CKV_ERR_ARG;
@@ -848,9 +885,16 @@ int enqueue_batch(ckv_ctx* c, const BatchItem* it, int n) {
     plan.add(&table[i], 2 * (size_t)std::max(it[i].pages->n_pages, 1));
   }
   const size_t copy_bytes = plan.total;
-  for (int i = 0; i < n; ++i) plan_measure(it[i].a, default_splits(it[i].a), it[i].o, plan, bufs[i]);
-  int rc = realize(c, plan);
-  if (rc) return rc;
+  size_t single = 0;
+  for (int i = 0; i < n; ++i) {
+    const size_t before = plan.total;
+    plan_measure(it[i].a, default_splits(it[i].a), it[i].o, plan, bufs[i]);
+    single = std::max(single, plan.total - before);
+  }
+  // as after single calls, the context holds what each problem alone needs
+  int rc = ensure_ws(c, single);
+  if (rc || (rc = ensure_batch_ws(c, plan.total))) return rc;
+  place(plan, c->batch_ws.p);
   MeasureBatch b{};
   b.n = n;
   b.D = it[0].a.D;
@@ -960,11 +1004,7 @@ extern "C" int ckv_measure_page_effects_noalloc(ckv_ctx* c, const ckv_kv_view* k
                 table + plan.total, (size_t)kScratchBytes);
   char* base = static_cast<char*>(c->scratch);
   int32_t* dtab = reinterpret_cast<int32_t*>(base);
-  size_t off = table;
-  for (auto& it : plan.items) {
-    *it.dst = base + off;
-    off += round_up(std::max<size_t>(it.bytes, 1), kAlign);
-  }
+  place(plan, base + table);
   if (n > 0) {
     CKV_HIP(c, hipMemcpyAsync(dtab, pages->start, n * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
     CKV_HIP(c, hipMemcpyAsync(dtab + n, pages->len, n * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
@@ -1020,9 +1060,9 @@ extern "C" int ckv_measure_page_effects_batch(ckv_ctx* c, int32_t n, const ckv_k
     }
     return CKV_OK;
   };
-  const size_t cap = c->ws_limit ? std::min(c->ws_limit, kBatchBytes) : kBatchBytes;
   for (int i = 0; i < n;) {
     int m = 0;
+    size_t single = 0;
     ckv::RunMemory mem;
     for (size_t total = 0; i + m < n && m < kBatchMax && same_kernels(items[i], items[i + m]); ++m) {
       const ItemMemory im(items[i + m]);
@@ -1033,7 +1073,8 @@ extern "C" int ckv_measure_page_effects_batch(ckv_ctx* c, int32_t n, const ckv_k
       int32_t* table = nullptr;
       plan_item(items[i + m], plan, b, table);
       total += plan.total + round_up(sizeof(MeasureProb), kAlign);
-      if (m > 0 && total > cap) break;
+      single = std::max(single, plan.total);
+      if (m > 0 && total > std::min(batch_limit(c, single), kBatchBytes)) break;
     }
     int rc = m > 1 ? enqueue_batch(c, &items[i], m) : CKV_ERR_NOMEM;
     if (rc == CKV_ERR_NOMEM) {

@@ -77,7 +77,8 @@ def test_batch_is_the_single_calls(ckv, hq, hkv, d, W, G, paged, mass):
 
 def test_several_splits_per_workgroup_and_workspace_limit(ckv):
     """Twelve problems in one launch; then with a workspace that holds one
-    problem only, where they go out one by one; then one that holds two."""
+    problem only, where they go out one by one; then one that holds a run of
+    one beside it, and one that holds a run of two."""
     P, ctx0 = ckv
     pr = [_problem(P, 16, 8, 64, 4096 - 60 * i, 8, 16, False, seed=i) for i in range(12)]
     args = [[p[j] for p in pr] for j in range(3)]
@@ -87,7 +88,7 @@ def test_several_splits_per_workgroup_and_workspace_limit(ckv):
     P.ckv_measure_page_effects(one, *pr[0][:3], want=WANT)
     need = one.workspace_bytes()
     one.close()
-    for limit in (need, 2 * need + 65536):
+    for limit in (need, 2 * need + 65536, 3 * need + 131072):
         ctx = P.Context(0)
         ctx.set_workspace_limit(limit)
         got = P.ckv_measure_page_effects_batch(ctx, *args, want=WANT)
@@ -123,3 +124,33 @@ def test_problems_that_share_an_output(ckv, shared):
                 continue
             got = outs[key][i][:size(key, p)]
             assert torch.equal(got.view(torch.int32), s[key].reshape(-1).view(torch.int32)), f"problem {i} {key}"
+
+
+def test_single_calls_keep_their_memory(ckv):
+    """A graph of a single call stays valid when a batch of such problems grows
+    the context's memory, and gives the single call's results."""
+    P, _ = ckv
+    stream = torch.cuda.Stream()
+    pr = [_problem(P, 8, 2, 64, 3000 + 50 * i, 8, 16, False, seed=80 + i) for i in range(8)]
+    torch.cuda.synchronize()
+    ctx = P.Context(0, stream)
+    with torch.cuda.stream(stream):
+        ref = [P.ckv_measure_page_effects(ctx, *p[:3], want=WANT) for p in pr]
+        held = ctx.workspace_bytes()
+        R = torch.empty(pr[0][2].n, device="cuda")
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            P.ckv_measure_page_effects(ctx, *pr[0][:3], R=R)
+        for _ in range(3):
+            got = P.ckv_measure_page_effects_batch(ctx, *[[p[j] for p in pr] for j in range(3)], want=WANT)
+            _same(got, ref, "batch")
+            # what the memory that the batch took in place of the calls' would hold by now
+            junk = torch.full((held // 4,), float("nan"), device="cuda")
+            R.fill_(-1)
+            graph.replay()
+            stream.synchronize()
+            assert torch.equal(R.view(torch.int32), ref[0]["R"].view(torch.int32))
+            del junk
+    assert ctx.workspace_bytes() > 2 * held
+    del graph
+    ctx.close()
