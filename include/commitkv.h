@@ -349,7 +349,10 @@ int ckv_measure_page_effects_noalloc(ckv_ctx* ctx, const ckv_kv_view* kv,
  * own beside the one of the single calls: it holds what all problems of a run
  * need, at most 384 MiB, counts toward ckv_workspace_bytes and the limit of
  * ckv_set_workspace_limit, and is freed by ckv_destroy or when a single call
- * needs its room; problems whose workspace does not fit run one by one.  A workspace or HIP failure part-way returns the error; the outputs of
+ * needs its room; problems whose workspace does not fit run one by one.  Under
+ * stream capture the problems are recorded one by one, and, as for every
+ * call, an equal call made before the capture leaves what it needs on the
+ * device (workspace and page tables).  A workspace or HIP failure part-way returns the error; the outputs of
  * the run it names are not valid, those of the earlier problems are enqueued.
  */
 int ckv_measure_page_effects_batch(ckv_ctx* ctx, int32_t n,

@@ -340,6 +340,17 @@ int upload(ckv_ctx* c, const void* src, size_t bytes, void* dst) {
   return CKV_OK;
 }
 
+// the cached device copy of an int32 array, or null
+const int32_t* find_copy(ckv_ctx* c, const std::vector<int32_t>& key) {
+  ++c->tick;
+  for (auto& e : c->pages)
+    if (e.key == key) {
+      e.used = c->tick;
+      return e.dev;
+    }
+  return nullptr;
+}
+
 // device copy of an int32 array, cached by content: an unchanged array is
 // not copied again (the entries have their own allocations, so later calls'
 // workspace never overwrites them)
@@ -350,14 +361,7 @@ int upload(ckv_ctx* c, const void* src, size_t bytes, void* dst) {
 // such a call instead of overwriting or freeing a table the call's kernels
 // are about to read.
 int cached_copy(ckv_ctx* c, std::vector<int32_t>&& key, const int32_t** dev) {
-  ++c->tick;
-  for (auto& e : c->pages) {
-    if (e.key == key) {
-      e.used = c->tick;
-      *dev = e.dev;
-      return CKV_OK;
-    }
-  }
+  if ((*dev = find_copy(c, key))) return CKV_OK;
   PageEntry* e = nullptr;
   if ((int)c->pages.size() < kPageCacheEntries) {
     c->pages.emplace_back();
@@ -865,26 +869,35 @@ struct ItemMemory {
 constexpr size_t kBatchBytes = size_t(384) << 20;
 constexpr int kBatchMax = 4096;   // problems of one launch (grid z)
 
-// Workspace of one problem of a batch (its page table is copied there too).
-void plan_item(const BatchItem& it, Plan& plan, MeasureBufs& b, int32_t*& table) {
-  plan_measure(it.a, default_splits(it.a), it.o, plan, b);
-  plan.add(&table, 2 * (size_t)std::max(it.pages->n_pages, 1));
-}
+// The page lists of a batch call in one array, one device copy for all its
+// runs: start[0..n) then len[0..n) of problem i at off[i] (neighbours that
+// share their host arrays share the copy).
+struct BatchTables {
+  std::vector<int32_t> key;
+  std::vector<size_t> off;
+  explicit BatchTables(const std::vector<BatchItem>& items) : off(items.size()) {
+    for (size_t i = 0; i < items.size(); ++i) {
+      const ckv_page_list &pl = *items[i].pages, &last = *items[i ? i - 1 : 0].pages;
+      if (i > 0 && pl.start == last.start && pl.len == last.len && pl.n_pages == last.n_pages) {
+        off[i] = off[i - 1];
+        continue;
+      }
+      off[i] = key.size();
+      if (pl.n_pages == 0) continue;
+      key.insert(key.end(), pl.start, pl.start + pl.n_pages);
+      key.insert(key.end(), pl.len, pl.len + pl.n_pages);
+    }
+  }
+};
 
 // Enqueues problems it[0 .. n), which agree in their kernels, as one launch
-// per kernel.  CKV_ERR_NOMEM (nothing enqueued) if their workspace cannot be had.
-int enqueue_batch(ckv_ctx* c, const BatchItem* it, int n) {
+// per kernel; `off`: their page lists in `tables`.  CKV_ERR_NOMEM (nothing
+// enqueued) if their workspace cannot be had.
+int enqueue_batch(ckv_ctx* c, const BatchItem* it, int n, const BatchTables& tables, const size_t* off) {
   Plan plan;
   std::vector<MeasureBufs> bufs(n);
-  std::vector<int32_t*> table(n, nullptr);
   MeasureProb* dev = nullptr;
-  // the arguments and the page tables first, so that one copy brings them
   plan.add(&dev, n);
-  size_t head = plan.total;
-  for (int i = 0; i < n; ++i) {
-    plan.add(&table[i], 2 * (size_t)std::max(it[i].pages->n_pages, 1));
-  }
-  const size_t copy_bytes = plan.total;
   size_t single = 0;
   for (int i = 0; i < n; ++i) {
     const size_t before = plan.total;
@@ -895,6 +908,9 @@ int enqueue_batch(ckv_ctx* c, const BatchItem* it, int n) {
   int rc = ensure_ws(c, single);
   if (rc || (rc = ensure_batch_ws(c, plan.total))) return rc;
   place(plan, c->batch_ws.p);
+  // the page tables stay cached, for the next call and for record_in_order
+  const int32_t* dtab = find_copy(c, tables.key);
+  if (!dtab && !tables.key.empty() && (rc = cached_copy(c, std::vector<int32_t>(tables.key), &dtab))) return rc;
   MeasureBatch b{};
   b.n = n;
   b.D = it[0].a.D;
@@ -915,19 +931,15 @@ int enqueue_batch(ckv_ctx* c, const BatchItem* it, int n) {
   for (int i = 0; i < n; ++i)
     units += (int64_t)bufs[i].sp.n_splits * it[i].a.Hkv * ceil_div(it[i].a.rows, 32 * b.nw);
   const int per = (int)std::max<int64_t>(1, units / (3 * resident));
-  std::vector<char> blob(copy_bytes, 0);
+  std::vector<MeasureProb> args(n);
   for (int i = 0; i < n; ++i) {
     const BatchItem& x = it[i];
     const int np = x.pages->n_pages;
-    MeasureProb p = make_prob(c, x.a, bufs[i], table[i], table[i] + np, np, b.nw, std::max(2 * resident / n, 1), x.R,
-                              x.R_head, x.lse, x.mass);
+    const int32_t* start = np > 0 ? dtab + off[i] : nullptr;
+    MeasureProb& p = args[i];
+    p = make_prob(c, x.a, bufs[i], start, np > 0 ? start + np : nullptr, np, b.nw, std::max(2 * resident / n, 1), x.R,
+                  x.R_head, x.lse, x.mass);
     p.splits_per_block = std::min(per, p.sp.n_splits);
-    std::memcpy(blob.data() + i * sizeof(MeasureProb), &p, sizeof p);
-    if (np > 0) {
-      std::memcpy(blob.data() + head, x.pages->start, np * sizeof(int32_t));
-      std::memcpy(blob.data() + head + np * sizeof(int32_t), x.pages->len, np * sizeof(int32_t));
-    }
-    head += round_up(2 * (size_t)std::max(np, 1) * sizeof(int32_t), kAlign);
     b.any_pages = b.any_pages || np > 0;
     b.max_split_groups = std::max(b.max_split_groups, ceil_div(p.sp.n_splits, p.splits_per_block));
     b.max_heads = std::max(b.max_heads, x.a.Hkv);
@@ -936,7 +948,7 @@ int enqueue_batch(ckv_ctx* c, const BatchItem* it, int n) {
     b.max_page_blocks = std::max(b.max_page_blocks, ceil_div(np, p.pw.items_per_block));
     b.max_mass_x = std::max(b.max_mass_x, ceil_div(x.a.S, p.mass_chunk));
   }
-  if ((rc = upload(c, blob.data(), blob.size(), dev))) return rc;
+  if ((rc = upload(c, args.data(), n * sizeof(MeasureProb), dev))) return rc;
   CKV_LAUNCH(c, "window_attention", launch_measure_batch(dev, b, 0, c->stream));
   CKV_LAUNCH(c, "combine", launch_measure_batch(dev, b, 1, c->stream));
   b.mass_fixup = b.any_pages && it[0].mass && mass_fixup_applies(it[0].a, mass_chunk(it[0].a));
@@ -945,6 +957,42 @@ int enqueue_batch(ckv_ctx* c, const BatchItem* it, int n) {
     if (!b.mass_fixup) CKV_LAUNCH(c, "page_fixup", launch_measure_batch(dev, b, 3, c->stream));
   }
   if (it[0].mass) CKV_LAUNCH(c, b.mass_fixup ? "token_mass_fixup" : "token_mass", launch_measure_batch(dev, b, 4, c->stream));
+  return CKV_OK;
+}
+
+bool capturing(ckv_ctx* c) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
+// Records problems it[0 .. n) one after another.  The arguments of a run are
+// copied to the device through pinned memory that later calls reuse, which a
+// replay would read again, so under stream capture nothing is copied: the
+// kernels take their arguments by value and the page tables that a call
+// before the capture left on the device.  CKV_ERR_NOMEM (nothing recorded) if
+// there are none or the workspace cannot be had.
+int record_in_order(ckv_ctx* c, const BatchItem* it, int n, const BatchTables& tables, const size_t* off) {
+  const int32_t* dtab = find_copy(c, tables.key);
+  if (!dtab && !tables.key.empty()) return CKV_ERR_NOMEM;
+  std::vector<Plan> plans(n);
+  std::vector<MeasureBufs> bufs(n);
+  size_t need = 0;
+  for (int i = 0; i < n; ++i) {
+    plan_measure(it[i].a, default_splits(it[i].a), it[i].o, plans[i], bufs[i]);
+    need = std::max(need, plans[i].total);
+  }
+  if (int rc = ensure_ws(c, need)) return rc;
+  for (int i = 0; i < n; ++i) {
+    const BatchItem& x = it[i];
+    const int np = x.pages->n_pages;
+    const int32_t* start = np > 0 ? dtab + off[i] : nullptr;
+    place(plans[i], c->ws.p);
+    if (int rc = enqueue_measure(c, x.a, bufs[i], start, np > 0 ? start + np : nullptr, x.pages, x.R, x.R_head, x.lse,
+                                 x.mass))
+      return rc;
+  }
   return CKV_OK;
 }
 
@@ -1060,6 +1108,8 @@ extern "C" int ckv_measure_page_effects_batch(ckv_ctx* c, int32_t n, const ckv_k
     }
     return CKV_OK;
   };
+  const bool record = capturing(c);
+  const BatchTables tables(items);
   for (int i = 0; i < n;) {
     int m = 0;
     size_t single = 0;
@@ -1070,13 +1120,14 @@ extern "C" int ckv_measure_page_effects_batch(ckv_ctx* c, int32_t n, const ckv_k
       mem.add(im.reads, im.writes);
       Plan plan;
       MeasureBufs b;
-      int32_t* table = nullptr;
-      plan_item(items[i + m], plan, b, table);
+      plan_measure(items[i + m].a, default_splits(items[i + m].a), items[i + m].o, plan, b);
       total += plan.total + round_up(sizeof(MeasureProb), kAlign);
       single = std::max(single, plan.total);
       if (m > 0 && total > std::min(batch_limit(c, single), kBatchBytes)) break;
     }
-    int rc = m > 1 ? enqueue_batch(c, &items[i], m) : CKV_ERR_NOMEM;
+    int rc = CKV_ERR_NOMEM;
+    if (record) rc = record_in_order(c, &items[i], m, tables, &tables.off[i]);
+    else if (m > 1) rc = enqueue_batch(c, &items[i], m, tables, &tables.off[i]);
     if (rc == CKV_ERR_NOMEM) {
       c->err.clear();
       for (int k = 0; k < m; ++k)

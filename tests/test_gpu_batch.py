@@ -154,3 +154,37 @@ def test_single_calls_keep_their_memory(ckv):
     assert ctx.workspace_bytes() > 2 * held
     del graph
     ctx.close()
+
+
+def test_batch_under_capture(ckv):
+    """A batch call recorded in a graph after an equal one: every replay, with
+    other inputs and with eager batches of other problems in between (which
+    reuse the pinned memory that eager batches pass their arguments through),
+    gives the single calls' results."""
+    P, _ = ckv
+    stream = torch.cuda.Stream()
+    pr = [_problem(P, 8, 2, 64, S, 8, 16, False, seed=90 + i, pages=i != 1) for i, S in enumerate((900, 700, 820))]
+    other = [_problem(P, 8, 2, 64, 2000 + 60 * i, 8, 24, False, seed=95 + i) for i in range(5)]
+    torch.cuda.synchronize()
+    ctx = P.Context(0, stream)
+    with torch.cuda.stream(stream):
+        args = [[p[j] for p in pr] for j in range(3)]
+        P.ckv_measure_page_effects_batch(ctx, *args, want=WANT)
+        R = [torch.empty(max(p[2].n, 1), device="cuda") for p in pr]
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            got = P.ckv_measure_page_effects_batch(ctx, *args, R=R, want=WANT)
+        for rep in range(4):
+            for _ in range(5):
+                P.ckv_measure_page_effects_batch(ctx, *[[p[j] for p in other] for j in range(3)], want=WANT)
+            for p in pr:
+                p[3][2].mul_(-1 if rep % 2 else 0.5)   # the queries
+            for x in got:
+                for key in WANT:
+                    x[key].fill_(-1)
+            graph.replay()
+            stream.synchronize()
+            _same(got, [P.ckv_measure_page_effects(ctx, *p[:3], want=WANT) for p in pr], f"replay {rep}")
+    del graph
+    ctx.sync()
+    ctx.close()
