@@ -758,10 +758,9 @@ int check_measure(ckv_ctx* c, const ckv_kv_view* kv, const ckv_window_view* win,
   return CKV_OK;
 }
 
-// what the kernels of one problem read (page_blocks: page workgroups of nw
-// waves aimed at)
+// what the kernels of one problem read (page_share: pages per page workgroup)
 MeasureProb make_prob(const ckv_ctx* c, const AttnGeom& a, const MeasureBufs& b, const int32_t* dstart,
-                      const int32_t* dlen, int n, int nw, int page_blocks, float* R, float* R_head, float* lse,
+                      const int32_t* dlen, int n, int page_share, float* R, float* R_head, float* lse,
                       float* token_mass) {
   const int total_rows = a.Hq * a.W;
   MeasureProb p;
@@ -781,7 +780,7 @@ MeasureProb make_prob(const ckv_ctx* c, const AttnGeom& a, const MeasureBufs& b,
   pw.len = dlen;
   pw.n_items = n;
   pw.n_pages = n;
-  pw.items_per_block = items_per_block(a, n, nw, page_blocks);
+  pw.items_per_block = page_share;
   pw.R = R;
   pw.R_head = R_head;
   pw.lse_scale = 1.f;
@@ -801,7 +800,8 @@ int enqueue_measure(ckv_ctx* c, const AttnGeom& a, const MeasureBufs& b, const i
                     const int32_t* dlen, const ckv_page_list* pages, float* R, float* R_head, float* lse,
                     float* token_mass) {
   const int n = pages->n_pages, max_len = max_page_len(pages);
-  const MeasureProb p = make_prob(c, a, b, dstart, dlen, n, max_waves(), kTargetBlocks, R, R_head, lse, token_mass);
+  const int share = items_per_block(a, n, max_waves(), kTargetBlocks);
+  const MeasureProb p = make_prob(c, a, b, dstart, dlen, n, share, R, R_head, lse, token_mass);
   CKV_LAUNCH(c, "window_attention", launch_window_attention(a, b.sp, c->stream));
   CKV_LAUNCH(c, "combine", launch_combine(a, b.sp, b.rs, lse, p.zl, c->stream));
   if (n > 0) {
@@ -868,6 +868,10 @@ struct ItemMemory {
 // itself, and 8 share a launch.
 constexpr size_t kBatchBytes = size_t(384) << 20;
 constexpr int kBatchMax = 4096;   // problems of one launch (grid z)
+// What a workgroup of a batch costs before its first tile and after its last
+// one, in tiles of the window kernel and pages of the page kernel (0 to 4
+// tiles and 1.5 to 6 pages measure alike, 0 pages up to 40% longer).
+constexpr float kStartTiles = 2.f, kStartPages = 3.f;
 
 // The page lists of a batch call in one array, one device copy for all its
 // runs: start[0..n) then len[0..n) of problem i at off[i] (neighbours that
@@ -923,23 +927,31 @@ int enqueue_batch(ckv_ctx* c, const BatchItem* it, int n, const BatchTables& tab
   // (pair, part) items of a fix-up list are a chain of latencies each, so a
   // problem's list gets a block per item where it is short
   b.fix_blocks = std::max(32, 8 * kTargetBlocks / n);
-  // the workgroups of the window and page kernels that the device holds at
-  // once; each takes about a third of its even share of the batch's splits
-  // and half of its share of the pages, so the last ones to finish idle little
+  // shares of the window kernel's splits and of the page kernel's pages: up to
+  // two 4-wave workgroups or one of 8 waves are resident per compute unit
   const int resident = kTargetBlocks * (b.nw == 4 ? 2 : 1);
-  int64_t units = 0;
-  for (int i = 0; i < n; ++i)
-    units += (int64_t)bufs[i].sp.n_splits * it[i].a.Hkv * ceil_div(it[i].a.rows, 32 * b.nw);
-  const int per = (int)std::max<int64_t>(1, units / (3 * resident));
+  ckv::Shares splits, items;
+  int64_t tiles = 0, n_splits = 0;
+  int most = INT_MAX;
+  for (int i = 0; i < n; ++i) {
+    const AttnGeom& a = it[i].a;
+    const int u = a.Hkv * ceil_div(a.rows, 32 * b.nw);
+    splits.add(bufs[i].sp.n_splits, u);
+    items.add(it[i].pages->n_pages, u);
+    tiles += ceil_div(a.S, 64);
+    n_splits += bufs[i].sp.n_splits;
+    most = std::min(most, page_items_limit(b.nw, a.W, a.group));
+  }
+  const int split_share = splits.best(resident, INT_MAX, kStartTiles * n_splits / tiles);
+  const int page_share = items.best(resident, most, kStartPages);
   std::vector<MeasureProb> args(n);
   for (int i = 0; i < n; ++i) {
     const BatchItem& x = it[i];
     const int np = x.pages->n_pages;
     const int32_t* start = np > 0 ? dtab + off[i] : nullptr;
     MeasureProb& p = args[i];
-    p = make_prob(c, x.a, bufs[i], start, np > 0 ? start + np : nullptr, np, b.nw, std::max(2 * resident / n, 1), x.R,
-                  x.R_head, x.lse, x.mass);
-    p.splits_per_block = std::min(per, p.sp.n_splits);
+    p = make_prob(c, x.a, bufs[i], start, np > 0 ? start + np : nullptr, np, page_share, x.R, x.R_head, x.lse, x.mass);
+    p.splits_per_block = std::min(split_share, p.sp.n_splits);
     b.any_pages = b.any_pages || np > 0;
     b.max_split_groups = std::max(b.max_split_groups, ceil_div(p.sp.n_splits, p.splits_per_block));
     b.max_heads = std::max(b.max_heads, x.a.Hkv);
@@ -1093,7 +1105,7 @@ extern "C" int ckv_measure_page_effects_batch(ckv_ctx* c, int32_t n, const ckv_k
   // runs of problems that share their kernels, whose workspace stays bounded
   // and of which none writes what another one reads or writes go out
   // together, the rest one by one: the results are those of single calls in
-  // order (40 layers: 5-10 us of host work)
+  // order
   std::vector<BatchItem> items(n);
   for (int i = 0; i < n; ++i)
     items[i] = BatchItem{make_geom(c, &kv[i], &win[i]), &pages[i], max_page_len(&pages[i]), R[i],

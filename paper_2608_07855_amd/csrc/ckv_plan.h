@@ -73,6 +73,55 @@ class RunMemory {
   RangeSet r_, w_;
 };
 
+// Units that one workgroup of a launch takes (pages, or splits of a row block).
+// Problem i has n[i] units in each of u[i] places, the device holds `resident`
+// workgroups at once, and a workgroup costs its units and `start` units to
+// begin.  The launch lasts as many rounds as its workgroups fill the device,
+// so the share is the smallest one that fits into the number of rounds for
+// which rounds * (share + start) is least: shares between those only add a
+// nearly empty last round (three problems of 1024 pages in 32 places: 193
+// pages a workgroup made 576 workgroups, three rounds of 256, and took 1.5
+// times as long as three launches).
+class Shares {
+ public:
+  void add(int n, int u) {
+    if (n <= 0 || u <= 0) return;
+    if (!g_.empty() && g_.back().n == n) g_.back().u += u;
+    else g_.push_back({n, u});
+    most_ = std::max(most_, n);
+    total_ += (int64_t)n * u;
+  }
+  int64_t workgroups(int share) const {
+    int64_t b = 0;
+    for (const Group& g : g_) b += ((g.n - 1) / share + 1) * g.u;
+    return b;
+  }
+  int best(int resident, int limit, float start) const {
+    limit = std::max(1, std::min(limit, most_));
+    if (g_.empty()) return limit;
+    const int64_t min_rounds = (workgroups(limit) - 1) / resident + 1;
+    int best = limit;
+    float least = -1.f;
+    for (int64_t r = std::max<int64_t>(1, min_rounds); r < min_rounds + 8; ++r) {
+      int share = (int)std::min<int64_t>(limit, std::max<int64_t>(1, (total_ - 1) / (r * resident) + 1));
+      while (share < limit && workgroups(share) > r * resident) ++share;
+      const float cost = r * (share + start);
+      if (least < 0.f || cost < least) {
+        least = cost;
+        best = share;
+      }
+      if (share == 1) break;
+    }
+    return best;
+  }
+
+ private:
+  struct Group { int n; int64_t u; };
+  std::vector<Group> g_;
+  int most_ = 0;
+  int64_t total_ = 0;
+};
+
 // Workgroups of the joint test (8 waves each) for so many window rows: about
 // one row per wave, at most as many as the device holds at once and one per
 // compute unit of a whole device.

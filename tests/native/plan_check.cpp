@@ -101,9 +101,51 @@ static void joint_workgroups() {
   CHECK(joint_state_global(64 * 128, 32) && !joint_state_global(32 * 64, 32));
 }
 
+// Shares against every share: within the limit, and no share that needs up to 7
+// rounds more than the fewest possible gives a cheaper launch
+static void shares() {
+  std::mt19937 rng(4);
+  for (int trial = 0; trial < 3000; ++trial) {
+    Shares s;
+    struct Problem { int n, u; };
+    std::vector<Problem> ps;
+    for (int k = 1 + rng() % 8; k > 0; --k) {
+      Problem p{(int)(rng() % (trial % 2 ? 40 : 300)), (int)(1 + rng() % 64)};
+      if (k % 3 == 0 && !ps.empty()) p = ps.back();
+      ps.push_back(p);
+      s.add(p.n, p.u);
+    }
+    auto blocks = [&](int share) {
+      int64_t b = 0;
+      for (const Problem& p : ps) b += (int64_t)((p.n + share - 1) / share) * p.u;
+      return b;
+    };
+    const int resident = trial % 3 ? 256 : 512, limit = 1 + rng() % 256;
+    const float start = (rng() % 9) * 0.5f;
+    const int best = s.best(resident, limit, start);
+    CHECK(best >= 1 && best <= limit);
+    int most = 1;
+    for (const Problem& p : ps) most = std::max(most, p.n);
+    if (blocks(1) == 0) continue;
+    auto rounds = [&](int share) { return (blocks(share) + resident - 1) / resident; };
+    const int top = std::min(limit, most);
+    const float cost = rounds(best) * (best + start);
+    for (int share = 1; share <= top; ++share) {
+      CHECK(s.workgroups(share) == blocks(share));
+      if (rounds(share) < rounds(top) + 8) CHECK(cost <= rounds(share) * (share + start) * 1.0001f);
+    }
+  }
+  // three problems of 1024 pages in 32 places: whole rounds
+  Shares s;
+  for (int i = 0; i < 3; ++i) s.add(1024, 32);
+  CHECK(s.workgroups(s.best(256, 256, 3.f)) % 256 == 0);
+  CHECK(Shares().best(256, 64, 3.f) == 1);
+}
+
 int main() {
   range_set();
   run_memory();
+  shares();
   joint_workgroups();
   joint_fixup();
   std::printf("plan checks passed\n");
