@@ -872,6 +872,17 @@ constexpr int kBatchMax = 4096;   // problems of one launch (grid z)
 // one, in tiles of the window kernel and pages of the page kernel (0 to 4
 // tiles and 1.5 to 6 pages measure alike, 0 pages up to 40% longer).
 constexpr float kStartTiles = 2.f, kStartPages = 3.f;
+// A problem of 8-wave workgroups with more window tiles per compute unit than
+// this goes out alone.  Against single calls, 2-8 problems of 32 tiles (65536
+// tokens and 256 window rows per KV head, or 16384 and 1024) run at 0.96-1.09 of
+// their speed together, 64 and 128 tiles at 0.91-1.02, mostly 0.97.
+// 4-wave workgroups gain at every size (1.03-1.34 at 32 tiles).
+constexpr int kAloneTiles = 48;
+bool goes_alone(const AttnGeom& a) {
+  const int nw = batch_waves(a.rows);
+  return nw == max_waves() &&
+         (int64_t)ceil_div(a.S, 64) * a.Hkv * ceil_div(a.rows, 32 * nw) > (int64_t)kAloneTiles * kTargetBlocks;
+}
 
 // The page lists of a batch call in one array, one device copy for all its
 // runs: start[0..n) then len[0..n) of problem i at off[i] (neighbours that
@@ -1128,7 +1139,7 @@ extern "C" int ckv_measure_page_effects_batch(ckv_ctx* c, int32_t n, const ckv_k
     ckv::RunMemory mem;
     for (size_t total = 0; i + m < n && m < kBatchMax && same_kernels(items[i], items[i + m]); ++m) {
       const ItemMemory im(items[i + m]);
-      if (m > 0 && !mem.independent(im.reads, im.writes)) break;
+      if (m > 0 && (goes_alone(items[i + m].a) || !mem.independent(im.reads, im.writes))) break;
       mem.add(im.reads, im.writes);
       Plan plan;
       MeasureBufs b;
@@ -1136,6 +1147,10 @@ extern "C" int ckv_measure_page_effects_batch(ckv_ctx* c, int32_t n, const ckv_k
       total += plan.total + round_up(sizeof(MeasureProb), kAlign);
       single = std::max(single, plan.total);
       if (m > 0 && total > std::min(batch_limit(c, single), kBatchBytes)) break;
+      if (goes_alone(items[i].a)) {
+        m = 1;
+        break;
+      }
     }
     int rc = CKV_ERR_NOMEM;
     if (record) rc = record_in_order(c, &items[i], m, tables, &tables.off[i]);

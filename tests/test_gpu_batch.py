@@ -98,6 +98,15 @@ def test_several_splits_per_workgroup_and_workspace_limit(ckv):
         ctx.close()
 
 
+def test_problem_that_goes_out_alone(ckv):
+    """25000 tokens and 1024 window rows per KV head (391 x 8 x 4 window tiles,
+    more than 48 per compute unit) between problems that share a launch."""
+    P, ctx = ckv
+    pr = [_problem(P, 64, 8, 64, S, 128, 64, False, seed=70 + i) for i, S in enumerate((700, 1100, 25000, 900, 641, 25000))]
+    got = P.ckv_measure_page_effects_batch(ctx, *[[p[j] for p in pr] for j in range(3)], want=WANT)
+    _same(got, [P.ckv_measure_page_effects(ctx, *p[:3], want=WANT) for p in pr], "alone")
+
+
 @pytest.mark.parametrize("shared", ["o", "lse", "R", "R_head", "token_mass"])
 def test_problems_that_share_an_output(ckv, shared):
     """One buffer for the same output of every problem: the other outputs are
