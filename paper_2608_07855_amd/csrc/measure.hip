@@ -262,27 +262,6 @@ __device__ __forceinline__ f32x16 scores(const uint16_t* sK, int tb, int col, in
   return acc;
 }
 
-// the same with the K fragments read kPFS steps ahead of the products
-template <int D, int KP, int kPFS = 4>
-__device__ __forceinline__ f32x16 scores_pf(const uint16_t* sK, int tb, int col, int half,
-                                            const bf16x8 (&qf)[D / 16]) {
-  constexpr int KS = D / 16;
-  bf16x8 kf[KS];
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) kf[ks] = load_bf16x8(sK + (32 * tb + col) * KP + 16 * ks + 8 * half);
-  f32x16 acc = zero16();
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) acc = mfma_bf16(kf[ks], qf[ks], acc);
-  __builtin_amdgcn_sched_group_barrier(0x100, kPFS, 0);
-#pragma unroll
-  for (int i = 0; i < KS - kPFS; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-  }
-  __builtin_amdgcn_sched_group_barrier(0x008, kPFS, 0);
-  return acc;
-}
-
 // Rounds the 16 weights of a score block to float16 (the B operands of the
 // two 16-token steps of O^T += V^T P^T) and adds the ROUNDED weights to sum.
 // Normalising by the sum of exactly the weights that multiply V keeps the
