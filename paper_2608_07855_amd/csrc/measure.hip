@@ -29,8 +29,8 @@
 // its few workgroups are bound by the latency of their tiles, and the idle
 // waves help to stage them (40 window rows per KV head, 4224 tokens: window
 // kernel 11.1 us, 13.7 with 2 waves).  A batch of such problems has
-// workgroups to spare and takes 2 or 4 waves and one LDS buffer each, up to
-// four workgroups per compute unit.
+// workgroups to spare: up to 128 rows they take 4 waves and one LDS buffer
+// each, two workgroups per compute unit (three of the page kernel at d = 64).
 #include "ckv_device.h"
 #include "ckv_kernels.h"
 
@@ -40,8 +40,9 @@
 namespace ckv {
 
 constexpr int kNW = 8;               // waves per workgroup of the token mass, and NW at most
-// pages (or candidates) and (page, head) maxima of a page workgroup: with
-// 2 waves, four workgroups share a compute unit's LDS (40 KB each)
+// pages (or candidates) and (page, head) maxima of a page workgroup: 4-wave
+// workgroups share a compute unit with others and hold few pages each (41 KB
+// of LDS at d = 128 with these)
 constexpr int page_items_max(int nw) { return nw == kNW ? kPageItemsMax : 64; }
 constexpr int page_rmax_cap(int nw) { return nw == kNW ? kPageRmaxCap : 128 * nw; }
 // tile buffers in LDS: with two, a workgroup stages a tile beside the one it
@@ -1780,8 +1781,12 @@ hipError_t launch_combine(const AttnGeom& a, const AttnSplit& sp, const RowStats
                           const ZeroList& zl, hipStream_t s) {
   dim3 grid(combine_blocks(a)), block(256);
   // Two batches of splits in flight (324 registers) where the rows leave a SIMD
-  // one wave anyway: the kernel is a chain of load latencies there.  2048 tokens
-  // and 4 heads, whole call: 26.6 -> 25.2 us; 4224 tokens, 40 heads: 34.5 -> 34.0.
+  // one wave anyway: the kernel is a chain of load latencies there.  One batch ->
+  // two, kernel and whole call in us (six runs of a side differ by 0.1): d = 64,
+  // 2048 tokens and 4 heads 8.86 -> 8.19 and 27.5 -> 26.8; 8192 tokens and 16
+  // heads 12.89 -> 11.50 and 37.2 -> 35.9; d = 128, 4224 tokens and 40 heads of 8
+  // rows 8.71 -> 8.16 and 38.3 -> 38.0; 8192 tokens and 16 heads 12.78 -> 11.40
+  // and 36.7 -> 35.4; 32 heads of 32 rows 8.81 -> 8.73, the call alike.
   const bool two = sp.n_splits > kCombBatch && combine_blocks(a) <= 256;
 #define CKV_COMBINE(DD, GG) hipLaunchKernelGGL((combine_kernel<DD, GG>), grid, block, 0, s, a, sp, rs, lse_out, zl)
   if (a.D == 128) { if (two) CKV_COMBINE(128, 2); else CKV_COMBINE(128, 1); }
@@ -1920,7 +1925,12 @@ int mass_slices(const AttnGeom& a, int ppw) {
 // idle: at 2048 tokens and 4 heads the two take 9 us together and 7 + 8
 // apart.  Where the token mass fills the device its workgroups wait for the
 // fix-up's and slow them down: at 32768 tokens and 32 heads (512 workgroups)
-// 55-64 us together, 31 + 15 apart.
+// 55-64 us together, 31 + 15 apart.  Near the line the longer lists prefer
+// two launches and the shorter one; whole calls, together / apart in us: 192
+// workgroups (32 heads of 64 rows, d = 128) 50.0 / 51.4, (16 heads, d = 64)
+// 38.5 / 43.9; 256 of these 59.2 / 56.3 and 45.8 / 49.0, (40 heads of 8 rows)
+// 34.0 / 37.2; 320: 57.8 / 57.6, 45.3 / 50.0 and 34.7 / 38.9; 512: 66.2 / 63.8,
+// 54.4 / 55.5 and 41.1 / 41.8.
 bool mass_fixup_applies(const AttnGeom& a, int chunk) {
   const int ppw = mass_pairs_per_wave(a);
   return ppw > 0 && (a.S + chunk - 1) / chunk * a.Hkv * mass_slices(a, ppw) <= 256;

@@ -4,12 +4,14 @@ outputs and of the compaction's row batches, against plain torch in float64
 
 * Token mass: a workgroup's 8 waves take a (query head, 32-row block) pair
   each; more pairs go to further slices (the last one partly filled), heads of
-  16 row blocks take two pairs a wave, and head counts that do not fill a
-  workgroup the general form.  Tolerance: weights come from float32 scores of
+  16 row blocks take two pairs a wave, and heads that do not fill a workgroup
+  the general form, which holds every pair (more than rows / 32 where heads
+  round up).  Tolerance: weights come from float32 scores of
   exact bf16 products (1e-4 in the exponent at these sizes) and a log-sum-exp
   whose sum holds float16 weights (2^-11 relative at most): 1e-3.
-* Complement pass: pairs with A > 0.99 are spread over S / 128 parts, at most
-  128, alone or in the launch of the token mass.  2e-3, the score tolerance.
+* Complement pass: pairs with A > 0.99 are spread over parts of their row, at
+  most 32 while the pairs are few, in a launch of its own, with and without a
+  token mass after it.  2e-3, the score tolerance.
 """
 import math
 
