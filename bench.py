@@ -374,11 +374,15 @@ def stack_leg(steps, comp_reps=3):
 
 def joint_rounds(acc, window=32):
     """Rounds of the speculative joint test given its decisions: a round
-    tests the next `window` candidates and ends at the first accepted one."""
+    tests the next `window` candidates as if all were accepted and as if none
+    were, and decides the run of equal decisions at its start and the first
+    different one after it."""
     cur, rounds, n = 0, 0, len(acc)
     while cur < n:
-        hit = next((t for t in range(cur, min(cur + window, n)) if acc[t]), None)
-        cur = hit + 1 if hit is not None else cur + window
+        end, t = min(cur + window, n), cur
+        while t < end and acc[t] == acc[cur]:
+            t += 1
+        cur = min(t + 1, end)
         rounds += 1
     return rounds
 

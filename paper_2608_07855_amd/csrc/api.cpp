@@ -36,7 +36,7 @@ constexpr int kTargetBlocks = 256;     // one 8-wave workgroup per compute unit
 // the fix-up recomputes a dominant page's whole split for one row, so long
 // splits make it expensive: splits hold at most this many tokens
 constexpr int kMaxSplitTokens = 8192;
-// the token-mass kernel (64 VGPRs, 40 KB of LDS) keeps two workgroups per
+// the token-mass kernel (126 registers, 40 KB of LDS) keeps two workgroups per
 // compute unit busy: 512 token chunks measured 31.7 us against 35.3 us with 256
 constexpr int kMassBlocks = 512;
 
