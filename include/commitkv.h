@@ -459,10 +459,12 @@ int ckv_pool_scores(ckv_ctx* ctx, const float* score, float* out, int32_t n_seq,
  * pages->start[cand[i]] .. + len[cand[i]] is retired when
  * i < min(*n_cand, max_cand) and accepted[i] != 0.  `pages` is a host page
  * list (the one given to ckv_joint_test); cand, n_cand and accepted are
- * device arrays as produced by ckv_classify_pages and ckv_joint_test. */
+ * device arrays as produced by ckv_classify_pages and ckv_joint_test.  Entries
+ * from *n_cand on are ignored, but the first min(max_cand, pages->n_pages) of
+ * cand and accepted may be read. */
 typedef struct ckv_accepted_pages {
   const ckv_page_list* pages;
-  const int32_t* cand;       /* device int32[max_cand] */
+  const int32_t* cand;       /* device int32, max_cand or n_pages entries at least */
   const int32_t* n_cand;     /* device int32[1] */
   const uint8_t* accepted;   /* device uint8[max_cand] */
   int32_t max_cand;

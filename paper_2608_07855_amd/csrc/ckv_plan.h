@@ -73,6 +73,13 @@ class RunMemory {
   RangeSet r_, w_;
 };
 
+// Candidates of a checkpoint's accepted pages that are read before their number
+// is known: candidate arrays hold max_cand entries, or one per page where they
+// come from the classification.  Thread `tid` of `threads` reads candidate tid
+// of these and then, from first_candidate_left on, every threads-th of the rest.
+constexpr int candidates_ahead(int max_cand, int n_pages) { return std::min(max_cand, n_pages); }
+constexpr int first_candidate_left(int tid, int ahead, int threads) { return tid < ahead ? tid + threads : tid; }
+
 // Units that one workgroup of a launch takes (pages, or splits of a row block).
 // Problem i has n[i] units in each of u[i] places, the device holds `resident`
 // workgroups at once, and a workgroup costs its units and `start` units to

@@ -25,6 +25,7 @@
 //   pos'[s,j] = pos[s,I[j]], 16-byte vector copies of whole rows.
 #include "ckv_device.h"
 #include "ckv_kernels.h"
+#include "ckv_plan.h"
 
 namespace ckv {
 
@@ -569,7 +570,8 @@ __global__ __launch_bounds__(kQT) void select_grid(SelectArgs a) {
   // The loads of each thread's first pending page, retired page and accepted
   // candidate (with its page span) are issued before the LDS is cleared, so
   // their latencies overlap one another and the barrier; a candidate's flag
-  // and page index do not wait for the candidate count.
+  // and page index do not wait for the candidate count as far as every
+  // caller's arrays reach (candidates_ahead).
   float pr = 0.f;
   int pln = 0, pst = 0, rst = 0, rln = 0, ast = 0, aln = 0;
   if (tid < n) {
@@ -582,9 +584,10 @@ __global__ __launch_bounds__(kQT) void select_grid(SelectArgs a) {
     rln = a.ret_len[roff + tid];
   }
   int nc = 0;
+  const int ahead = candidates_ahead(ap.max_cand, ap.n_pages);
   if (ap.cand) {
     nc = min(*ap.n_cand, ap.max_cand);
-    if (tid < ap.max_cand) {
+    if (tid < ahead) {
       const uint8_t acc = ap.accepted[tid];
       const int pg = ap.cand[tid];
       if (acc && pg >= 0 && pg < ap.n_pages) {
@@ -612,9 +615,9 @@ __global__ __launch_bounds__(kQT) void select_grid(SelectArgs a) {
     const int st = a.ret_start[roff + i], ln = a.ret_len[roff + i];
     for (int t = max(st, c0); t < min(st + ln, c1); ++t) sRet[t - c0] = 1;
   }
-  if (tid < nc)
+  if (tid < min(nc, ahead))
     for (int t = max(ast, c0); t < min(ast + aln, c1); ++t) sRet[t - c0] = 1;
-  for (int i = tid + kQT; i < nc; i += kQT) {
+  for (int i = first_candidate_left(tid, ahead, kQT); i < nc; i += kQT) {
     if (!ap.accepted[i]) continue;
     const int pg = ap.cand[i];
     if (pg < 0 || pg >= ap.n_pages) continue;

@@ -142,10 +142,29 @@ static void shares() {
   CHECK(Shares().best(256, 64, 3.f) == 1);
 }
 
+// Candidates of a checkpoint: every one below the count is taken once, and
+// nothing past the shortest array that callers pass is read before the count
+static void candidates() {
+  for (int threads : {1, 4, 256})
+    for (int max_cand : {1, 2, 3, 7, 255, 256, 257, 600})
+      for (int n_pages : {0, 1, 2, 5, 113, 256, 300, 1000})
+        for (int nc = 0; nc <= max_cand; nc += 1 + max_cand / 9) {
+          const int ahead = candidates_ahead(max_cand, n_pages);
+          std::vector<int> taken(max_cand, 0);
+          for (int tid = 0; tid < threads; ++tid) {
+            if (tid < ahead) CHECK(tid < max_cand && tid < n_pages);
+            if (tid < std::min(nc, ahead)) ++taken[tid];
+            for (int i = first_candidate_left(tid, ahead, threads); i < nc; i += threads) ++taken[i];
+          }
+          for (int i = 0; i < max_cand; ++i) CHECK(taken[i] == (i < nc ? 1 : 0));
+        }
+}
+
 int main() {
   range_set();
   run_memory();
   shares();
+  candidates();
   joint_workgroups();
   joint_fixup();
   std::printf("plan checks passed\n");

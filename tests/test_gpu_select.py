@@ -259,3 +259,37 @@ def test_pool_scores(ckv, mode):
             assert np.all(out[s, nt[s]:] == 0)
     with pytest.raises(P.CKVError):
         P.ckv_pool_scores(ctx, torch.from_numpy(sc).cuda(), nt, 4, mode)     # even kernel
+
+
+@pytest.mark.parametrize("n_pages,n_cand,max_cand", [(5, 3, 256), (5, 5, 5), (113, 40, 256), (5, 300, 600),
+                                                     (300, 290, 400), (1, 0, 7)])
+def test_candidate_counts(ckv, n_pages, n_cand, max_cand):
+    """Accepted pages whose candidate array has as many entries as there are
+    pages (what the classification writes) under a larger max_cand, and more
+    candidates than pages (each page several times, accepted once)."""
+    P, ctx = ckv
+    S = 5000
+    print(f"[select] {n_pages} pages, {n_cand} of {max_cand} candidates", flush=True)
+    rng = np.random.default_rng(n_pages + n_cand)
+    start = (np.arange(n_pages) * 16 + 3).astype(np.int32)
+    entries = max(n_cand, min(max_cand, n_pages))
+    cand = np.arange(entries, dtype=np.int32) % n_pages
+    flags = np.zeros(max_cand, np.uint8)
+    flags[:n_cand] = rng.random(n_cand) < 0.3
+    if n_cand:
+        flags[n_cand - 1] = 1
+    flags[n_cand:] = 1                      # entries past the count are ignored
+    gone = {int(cand[i]) for i in range(n_cand) if flags[i]}
+    score = torch.rand((1, S), device="cuda")
+    k = torch.zeros((1, 1, 1, S, 64), dtype=torch.bfloat16, device="cuda")
+    pos = torch.arange(S, dtype=torch.int32, device="cuda")[None]
+    acc = (P.Pages(start, np.full(n_pages, 9, np.int32)), torch.from_numpy(cand).cuda(),
+           torch.tensor([n_cand], dtype=torch.int32, device="cuda"), torch.from_numpy(flags).cuda(), max_cand)
+    out = P.ckv_select_and_compact(ctx, k, k, pos, [S], score, [P.Pages([], [])], [P.Pages([], [])], [None], budget=S,
+                                   accepted=[acc], compact=False)
+    torch.cuda.synchronize()
+    keep = np.ones(S, bool)
+    for p in gone:
+        keep[start[p]:start[p] + 9] = False
+    nk = int(out["n_kept"][0].item())
+    np.testing.assert_array_equal(out["kept"][0, :nk].cpu().numpy(), np.flatnonzero(keep))
