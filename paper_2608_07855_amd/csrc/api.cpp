@@ -36,6 +36,11 @@ constexpr int kTargetBlocks = 256;     // one 8-wave workgroup per compute unit
 // the fix-up recomputes a dominant page's whole split for one row, so long
 // splits make it expensive: splits hold at most this many tokens
 constexpr int kMaxSplitTokens = 8192;
+// Working memory of the problems one launch serves together, at most.  At
+// 4224 tokens and 40 window rows per KV head (7 MB a problem) that is the
+// whole of a 40-layer commit; a 65536-token layer (45 MB) fills the device by
+// itself, and 8 share a launch.
+constexpr size_t kBatchBytes = size_t(384) << 20;
 // the token-mass kernel (126 registers, 40 KB of LDS) keeps two workgroups per
 // compute unit busy: 512 token chunks measured 31.7 us against 35.3 us with 256
 constexpr int kMassBlocks = 512;
@@ -241,9 +246,10 @@ int ensure_batch_ws(ckv_ctx* c, size_t need) {
   if (need <= c->batch_ws.cap) return CKV_OK;
   const size_t most = batch_limit(c, 0);
   if (need > most) return fail(c, CKV_ERR_NOMEM, "workspace of %zu bytes exceeds the limit", need);
+  const size_t want = std::min(most, std::max(need, std::min(kBatchBytes, c->batch_ws.cap + c->batch_ws.cap / 2)));
   CKV_HIP(c, hipStreamSynchronize(c->stream));
   release(c->batch_ws);
-  if (allocate(c->batch_ws, need)) return CKV_OK;
+  if (allocate(c->batch_ws, want) || (want > need && allocate(c->batch_ws, need))) return CKV_OK;
   return fail(c, CKV_ERR_NOMEM, "hipMalloc of %zu workspace bytes failed", need);
 }
 
@@ -862,11 +868,6 @@ struct ItemMemory {
   }
 };
 
-// Working memory of the problems one launch serves together, at most.  At
-// 4224 tokens and 40 window rows per KV head (7 MB a problem) that is the
-// whole of a 40-layer commit; a 65536-token layer (45 MB) fills the device by
-// itself, and 8 share a launch.
-constexpr size_t kBatchBytes = size_t(384) << 20;
 constexpr int kBatchMax = 4096;   // problems of one launch (grid z)
 // What a workgroup of a batch costs before its first tile and after its last
 // one, in tiles of the window kernel and pages of the page kernel (0 to 4
