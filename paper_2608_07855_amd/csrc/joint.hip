@@ -277,15 +277,18 @@ __device__ __forceinline__ void mark_accepted(const JointArgs& j, int ap, int t)
   __hip_atomic_fetch_min(&j.acc_t[ap], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The decision of a round from its maxima (the workgroup that arrives last);
-// the payload in thread 0.
-__device__ unsigned joint_decide(const JointArgs& j, int cursor, int n_eff, const unsigned* sRed,
-                                 const int* sRedAny) {
+// The decision of a round from its maxima (the workgroup that arrives last),
+// published in `word` under the wait's number.  What it stores besides is read
+// behind a later arrival of this workgroup only, so the word goes first and the
+// others do not wait for those stores; the loads leave before everything.
+__device__ void joint_decide(const JointArgs& j, int cursor, int n_eff, const unsigned* sRed, const int* sRedAny,
+                             unsigned long long* word, int epoch) {
   const int tid = threadIdx.x;
-  if (tid >= 64) return 0u;
+  if (tid >= 64) return;
   const int c = tid & 31, t = cursor + c;
   const float r = __uint_as_float(sRed[tid]);
   const bool any = sRedAny[tid] != 0, valid = t < n_eff;
+  const int ap = valid ? j.cand[t] : -1, n_listed = ld_agent(&j.ctrl[kFixN]);
   const unsigned long long bp = __ballot(valid && (j.accept_all || (r <= j.tau && !any)));
   const unsigned long long bf = __ballot(valid && !j.accept_all && r > j.tau);
   const unsigned long long ba = __ballot(any);
@@ -300,18 +303,17 @@ __device__ unsigned joint_decide(const JointArgs& j, int cursor, int n_eff, cons
   const int dec = n + (extra ? 1 : 0);
   const unsigned decided = dec >= 32 ? 0xffffffffu : (1u << dec) - 1u;
   const bool defer = j.want_union && ((unsigned)(chain ? ba >> 32 : ba) & decided) != 0u;
+  unsigned p = (chain ? kDecChain : 0u) | (unsigned)n << 1 | (extra ? kDecExtra : 0u) |
+               (resolve ? kDecResolve : 0u) | (defer ? kDecDefer : 0u);
+  // empty the list first unless it has room for a whole round's pairs
+  if ((defer || resolve) && n_listed > kJointWindow * j.total_rows) p |= kDecFlush;
+  if (tid == 0) st_agent(word, (unsigned long long)epoch << 32 | p);
   const bool mine = (tid >> 5) == (chain ? 1 : 0);   // the lanes that hold the chosen guess
   if (mine && (c < dec || (resolve && c == 0))) st_agent(&j.ur[t], r);
   if (mine && c < dec && (chain ? c < n : c == n)) {
     st_agent(&j.accepted[t], (uint8_t)1);
-    const int ap = j.cand[t];
     if (ap >= 0 && ap < j.n_pages) mark_accepted(j, ap, t);
   }
-  unsigned p = (chain ? kDecChain : 0u) | (unsigned)n << 1 | (extra ? kDecExtra : 0u) |
-               (resolve ? kDecResolve : 0u) | (defer ? kDecDefer : 0u);
-  // empty the list first unless it has room for a whole round's pairs
-  if ((defer || resolve) && ld_agent(&j.ctrl[kFixN]) > kJointWindow * j.total_rows) p |= kDecFlush;
-  return p;
 }
 
 struct JointSync {
@@ -350,12 +352,12 @@ __device__ bool joint_sync(const JointArgs& j, JointSync& sy, bool tests, int cu
       if (tid < 64) st_agent(&j.gmax[grp * 64 + tid], sy.sRed[tid] | (sy.sRedAny[tid] ? 0x80000000u : 0u));
     }
     if (arrive(&j.ctrl[kTop], sy.epoch * n_grp)) {
-      unsigned p = 0u;
       if (tests) {
         joint_reduce(j.gmax, n_grp, sy.sRed, sy.sRedAny);
-        p = joint_decide(j, cursor, n_eff, sy.sRed, sy.sRedAny);
+        joint_decide(j, cursor, n_eff, sy.sRed, sy.sRedAny, word, sy.epoch);
+      } else if (tid == 0) {
+        st_agent(word, (unsigned long long)sy.epoch << 32);
       }
-      if (tid == 0) st_agent(word, (unsigned long long)sy.epoch << 32 | p);
     }
   }
   __syncthreads();
